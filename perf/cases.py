@@ -17,8 +17,8 @@ seeded problems of `workload`. A case is a dict of plain values:
 A pass starts from the same iterate every time (the trajectories are restored
 and the multipliers cleared, as a program does that is handed new problems),
 except for "serve", whose instances go on from their last plan. A pass runs the
-SQP iterations of a control tick (one to three) and not those of a solve to
-convergence: there the best candidates of the line search tie below the FP32
+first SQP iterations (one to three in all) and not those of a solve to
+convergence: later the best candidates of the line search tie below the FP32
 resolution of the merit, so which one is taken, and with it the rest of the
 iterate, hangs on rounding. Each SQP iteration is the same work.
 """
@@ -56,10 +56,10 @@ def listed():
         dict(name="tip 7x32 M256", kind="task", n=7, N=32, M=256, iters=1),
         # A batch of mixed robots and horizons as one graph replay.
         dict(name="uneven M128", kind="uneven", M=128, iters=2, task=False),
-        # Closed-loop MPC: serving step and plant, two ticks.
-        dict(name="mpc 7x64 M256", kind="loop", n=7, N=64, M=256, iters=3, ticks=2),
+        # Closed-loop MPC: serving step and plant, a real-time iteration per tick.
+        dict(name="mpc 7x64 M256", kind="loop", n=7, N=64, M=256, iters=1, ticks=3),
         # Force estimation: 32 instances with 32 hypotheses each.
-        dict(name="forces 32x32", kind="forces", n=7, N=32, P=32, H=32, iters=2, ticks=2),
+        dict(name="forces 32x32", kind="forces", n=7, N=32, P=32, H=32, iters=1, ticks=2),
         # The plant of a simulation study on its own.
         dict(name="plant 7 M256", kind="plant", n=7, M=256, substeps=10),
     ]
@@ -88,10 +88,10 @@ def draw(rng):
         return dict(kind=kind, n=n, N=min(N, 64), M=pool, reqs=_log_int(rng, 1, min(32, pool)), iters=1)
     if kind == "loop":
         ticks = rng.randint(1, 2)
-        return dict(kind=kind, n=n, N=min(N, 64), M=most(2 * iters * ticks), iters=iters, ticks=ticks)
+        return dict(kind=kind, n=n, N=min(N, 64), M=most(2 * ticks), iters=1, ticks=ticks)
     if kind == "forces":
         return dict(kind=kind, n=rng.choice([6, 7]), N=min(max(N, 8), 32), P=rng.randint(1, 32), H=rng.randint(2, 32),
-                    iters=iters, ticks=rng.randint(1, 2))
+                    iters=1, ticks=rng.randint(1, 2))
     return dict(kind=kind, n=n, M=_log_int(rng, 1, 1024), substeps=rng.randint(1, 20))
 
 
