@@ -13,7 +13,9 @@
 //      Gauss-Jordan elimination (SPD, no pivoting).
 //   3. Stair preconditioner (Eq. (6)): the FP64 variants apply it factored,
 //      P v = D^-1 (v - O D^-1 v) with O the off-diagonal blocks of S~, so only
-//      the rows of D^-1 are kept; the all-FP32 variant's lanes of knot k+1 form
+//      the rows of D^-1 are kept, and take the S~ product of the result from the
+//      same two half-sweeps (pcg_half_sweeps; four knots per lane group apply
+//      both products in full); the all-FP32 variant's lanes of knot k+1 form
 //      the off-diagonal block -D_{k+1}^-1 phi_k D_k^-1 once and knot k reads
 //      its transpose. The paper's single grid-wide synchronisation becomes a
 //      workgroup barrier.
@@ -71,6 +73,22 @@ struct BlockStore {
   static constexpr int LB = kLds ? KN : 1;
 };
 
+// The FP64 variants with one or two knots per lane group run the PCG of
+// pcg_half_sweeps (below).
+template <class Real, int KPT>
+constexpr bool half_sweeps() {
+  return sizeof(Real) == 8 && KPT <= 2;
+}
+// Its vectors: knot k at row k + 1, zero rows beyond both ends. (K = 0: unused.)
+template <int ND, int K>
+struct PcgBufs {
+  static constexpr int KH = K * Shape<ND>::SLOTS + 2;
+  double z[KH][Shape<ND>::G];
+  double v[KH][Shape<ND>::G];
+  alignas(16) double red[128];   // per wavefront: four partial sums of each of two values, interleaved;
+                                 // [64, 128): written by the lanes without one, never read
+};
+
 template <int ND, int KPT, class Real>
 struct Smem {
   using Sh = Shape<ND>;
@@ -85,19 +103,22 @@ struct Smem {
   float e[KN][G];          // defects e_k = f(x_k, u_k) - x_{k+1}
   float qg[KN][G];         // state gradients q_k
   float rg[KN][8];         // control gradients r_k
-  Real rv[KN][G];          // PCG residual, shared for the preconditioner
-  Real gv[KN][G];          // gamma~, shared for the reference norm
   float qdd[KN][8];        // forward dynamics at the knot
   float Lf[KN][Sh::NL];    // packed Cholesky factor of the inertia matrix
-  Real pv[KN][G];          // vector shared for the S~ product
-  Real sv[KN][G];          // Q_k^-1 times pv
+  static constexpr bool kHalf = half_sweeps<Real, KPT>();
+  static constexpr int KV = kHalf ? 1 : KN;   // vectors of the other arrangements
+  Real rv[KV][G];          // PCG residual, shared for the preconditioner
+  Real gv[KV][G];          // gamma~, shared for the reference norm
+  Real pv[KV][G];          // vector shared for the S~ product
+  Real sv[KV][G];          // Q_k^-1 times pv
+  PcgBufs<ND, kHalf ? KPT : 0> pcg;
   double piv[Sh::SLOTS][G];  // Gauss-Jordan pivot rows, one per lane group
   double red[2][3][kBlock / 64];  // per-wavefront partial sums
   double mp0[KN];          // per-knot merit terms at the current point
   double Qi[G], Qni[G];    // 1 / (Q + rho), 1 / (Q_N + rho) for the current rho
   union {
     double mp[kMaxAlpha][KN];  // per-knot merit terms of the step candidates (line search)
-    Real tv[KN][G];            // exchange inside a lane group (PCG preconditioner)
+    Real tv[KV][G];            // exchange inside a lane group (PCG preconditioner)
   };
   double merit[kMaxAlpha + 1];
   float alpha[kMaxAlpha];
@@ -107,8 +128,9 @@ struct Smem {
                            // the blocks below 16-byte aligned for 128-bit LDS reads)
   float A[LB][NX * NX];    // A_k
   float B[LB][NX * NU];    // B_k
-  float Dinv[LB][NX * NX]; // inverse diagonal blocks of S~
-  float Poff[LB][NX * NX]; // P_{k+1,k}
+  static constexpr int LP = kHalf ? 1 : LB;
+  float Dinv[LP][NX * NX]; // inverse diagonal blocks of S~
+  float Poff[LP][NX * NX]; // P_{k+1,k}
 };
 
 // LDS of the task-space variant, placed after Smem.
@@ -191,11 +213,27 @@ __device__ __forceinline__ double lane_val(double v, int l) {
     [c6] "v"(c[6]), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]), [c11] "v"(c[11])
 #define GATO_C14(c) GATO_C12(c), [c12] "v"(c[12]), [c13] "v"(c[13])
 
-// acc += sum_m c[m] x_m, m = 0..NX-1 in order (x_m: x at lane m of the row).
+// Two 8-lane groups share a row: both groups' products in every lane, of which
+// each keeps its own. (Bank masks would keep them apart inside the chain, but a
+// masked fmac does not pass the other half's sum on to the next one.)
+#define GATO_NB8(M, H, S)                                                                  \
+  "v_fmac_f64_dpp %0, " S "%2, %[c" #M "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_fmac_f64_dpp %1, " S "%2, %[c" #M "] row_newbcast:" #H " row_mask:0xf bank_mask:0xf\n\t"
+#define GATO_DOT8(S)                                                                                            \
+  double hi = acc;                                                                                              \
+  asm volatile("s_nop 1\n\t" GATO_NB8(0, 8, S) GATO_NB8(1, 9, S) GATO_NB8(2, 10, S)                               \
+               GATO_NB8(3, 11, S) GATO_NB8(4, 12, S) GATO_NB8(5, 13, S)                                         \
+               : "+v"(acc), "+v"(hi) : "v"(x), [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]),                   \
+                 [c3] "v"(c[3]), [c4] "v"(c[4]), [c5] "v"(c[5]));                                                \
+  acc = (threadIdx.x & 8) ? hi : acc;
+
+// acc += sum_m c[m] x_m, m = 0..NX-1 in order (x_m: x at lane m of the group).
 template <int NX>
 __device__ __forceinline__ void row_dot1(double &acc, double x, const double *c) {
-  static_assert(NX == 12 || NX == 14, "16-lane groups hold 12 or 14 rows");
-  if constexpr (NX == 14) {
+  static_assert(NX == 6 || NX == 12 || NX == 14, "8-lane groups hold 6 rows, 16-lane groups 12 or 14");
+  if constexpr (NX == 6) {
+    GATO_DOT8("")
+  } else if constexpr (NX == 14) {
     asm volatile("s_nop 1\n\t" GATO_NB1(0, c) GATO_NB1(1, c) GATO_NB1(2, c) GATO_NB1(3, c) GATO_NB1(4, c)
                  GATO_NB1(5, c) GATO_NB1(6, c) GATO_NB1(7, c) GATO_NB1(8, c) GATO_NB1(9, c) GATO_NB1(10, c)
                  GATO_NB1(11, c) GATO_NB1(12, c) GATO_NB1(13, c)
@@ -213,8 +251,10 @@ __device__ __forceinline__ void row_dot1(double &acc, double x, const double *c)
 #define GATO_NBN(M, C) "v_fmac_f64_dpp %0, -%1, %[c" #M "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t"
 template <int NX>
 __device__ __forceinline__ void row_dot1_sub(double &acc, double x, const double *c) {
-  static_assert(NX == 12 || NX == 14, "16-lane groups hold 12 or 14 rows");
-  if constexpr (NX == 14) {
+  static_assert(NX == 6 || NX == 12 || NX == 14, "8-lane groups hold 6 rows, 16-lane groups 12 or 14");
+  if constexpr (NX == 6) {
+    GATO_DOT8("-")
+  } else if constexpr (NX == 14) {
     asm volatile("s_nop 1\n\t" GATO_NBN(0, c) GATO_NBN(1, c) GATO_NBN(2, c) GATO_NBN(3, c) GATO_NBN(4, c)
                  GATO_NBN(5, c) GATO_NBN(6, c) GATO_NBN(7, c) GATO_NBN(8, c) GATO_NBN(9, c) GATO_NBN(10, c)
                  GATO_NBN(11, c) GATO_NBN(12, c) GATO_NBN(13, c)
@@ -227,6 +267,8 @@ __device__ __forceinline__ void row_dot1_sub(double &acc, double x, const double
   }
 }
 #undef GATO_NBN
+#undef GATO_DOT8
+#undef GATO_NB8
 
 // acc += sgn * sum_m c[m] x_m with FP32 coefficients converted inside the
 // statement (two temporaries), m = 0..NX-1 in order; the same roundings as
@@ -361,14 +403,14 @@ __device__ __forceinline__ void gj_dpp(double *row, int lane, std::integer_seque
 // dependent chain sits between the inner products and the vector updates of
 // every iteration, it takes 1.4% off the one-knot-per-group joint-space call,
 // 2.7% off the two-knots-per-group call and 3% off the task-space call.
-__device__ __forceinline__ double div_pcg(double a, double b) {
+__device__ __forceinline__ double rcp_pcg(double b) {
   double r = __builtin_amdgcn_rcp(b);
   double e = fma(-b, r, 1.0);
   r = fma(r, e, r);
   e = fma(-b, r, 1.0);
-  r = fma(r, e, r);
-  return a * r;
+  return fma(r, e, r);
 }
+__device__ __forceinline__ double div_pcg(double a, double b) { return a * rcp_pcg(b); }
 __device__ __forceinline__ float div_pcg(float a, float b) { return a / b; }
 
 // Sum over the wavefront (all 64 lanes must be active).
@@ -432,6 +474,261 @@ __device__ __forceinline__ void block_sum(double (*red)[3][kBlock / 64], int &bu
     v[i] = s;
   }
   buf ^= 1;
+}
+
+// ---- PCG with the stair preconditioner in two half-sweeps (FP64).
+// With D and O the block diagonal and the block off-diagonal of S~, the
+// factored preconditioner of Eq. (6), P = D^-1 - D^-1 O D^-1, gives
+//   S~ P = (D + O) (D^-1 - D^-1 O D^-1) = I - (O D^-1)^2,
+// so one pass of
+//   z = D^-1 w,  y = O z,  v = D^-1 y,  m = P w = z - v,  n = S~ m = w - O v
+// forms both products of a pipelined iteration without the rows of D: four
+// block-row products fewer than P and S~ one after the other need (six against
+// seven), and 28 registers per knot of a lane group free. The rows of O are held
+// scaled, Am = -A_{k-1} Q_{k-1}^-1 and Ac = -Q_k^-1 A_k^T, so that one vector
+// (z, then v) is published per product. Rows that do not exist are zero and the
+// knots beyond the ends are zero rows of the buffers, so the loop has no masks.
+// Measured against P and S~ applied one after the other (us per PCG iteration,
+// MI355X): 7 DoF N = 32, 256 solves 1.49 -> 0.90; N = 64 3.07 -> 1.37 (two
+// knots per lane group: the A rows in FP64 and no spills in the loop); 6 DoF
+// N = 8 0.94 -> 0.55; tip tracking 7 DoF N = 32 1.54 -> 1.01. The loop of one
+// knot per lane group has 128 VALU instructions (237), 84 of them the products.
+
+// Two sums over the workgroup through the matrix cores: three v_mfma_f64_4x4x4
+// (lane = i + 4 block + 16 k for A, j + 4 block + 16 k for B, j + 4 block + 16 i
+// for the result) leave, per wavefront, the four blocks' sums of `a` in the even
+// columns and of `b` in the odd ones; BlockSums::get adds the 32 partials of each
+// after the barrier, in the same order in every lane. Against DPP butterflies and
+// a pairwise tree over broadcast reads this takes 9 instead of 54 VALU
+// instructions per wavefront off the loop, and 2 LDS reads instead of 8.
+__device__ __forceinline__ double block_sums_start(int tid, double a, double b) {
+  const double even = (tid & 1) ? 0.0 : 1.0;
+  const double d = __builtin_amdgcn_mfma_f64_4x4x4f64(a, even, 0.0, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(b, 1.0 - even, d, 0, 0, 0);
+}
+// (In the pipelined loop every lane writes: no exec mask splits the block that
+// the scheduler fills the sums' latency from.)
+__device__ __forceinline__ void block_sums_finish(double *red, int tid, double d) {
+  d = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, d, 0.0, 0, 0, 0);
+  const int l = tid & 63;
+  red[(l & 0x32) == 0 ? (tid >> 6) * 8 + (l >> 2) * 2 + (l & 1) : 64 + l] = d;
+}
+__device__ __forceinline__ void block_sums_put(double *red, int tid, double a, double b) {
+  const double d = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, block_sums_start(tid, a, b), 0.0, 0, 0, 0);
+  const int l = tid & 63;
+  if ((l & 0x32) == 0) red[(tid >> 6) * 8 + (l >> 2) * 2 + (l & 1)] = d;
+}
+struct BlockSums {
+  double x[4];
+  __device__ __forceinline__ void read(const double *red, int tid) {
+    const double *q = red + 4 * ((tid & 3) + 4 * ((tid & 63) >> 4));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = q[i];
+  }
+  __device__ __forceinline__ void get(double &a, double &b) const {
+    const double da = __builtin_amdgcn_mfma_f64_4x4x4f64(x[0] + x[2], 1.0, 0.0, 0, 0, 0);
+    const double db = __builtin_amdgcn_mfma_f64_4x4x4f64(x[1] + x[3], 1.0, 0.0, 0, 0, 0);
+    a = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, da, 0.0, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, db, 0.0, 0, 0, 0);
+  }
+};
+
+// Runs the PCG from lam (whose off-diagonal product still has to be taken off
+// the residual r = gamma~ - D lam) and updates lam. Am, Ac, Pd: this lane's rows
+// of the scaled off-diagonal blocks and of D^-1. Returns the iteration count;
+// capped: the tolerance was not reached. Per iteration (u = P r, w = S~ u by
+// recurrence):
+//   gamma = (r, u), delta = (w, u), m = P w, n = S~ m
+//   beta = gamma / gamma_prev, alpha = gamma / (delta - beta gamma / alpha_prev)
+//   z = n + beta z, q = m + beta q, s = w + beta s, p = u + beta p
+//   lambda += alpha p, r -= alpha s, u -= alpha q, w -= alpha z
+// PIPE = false (tip tracking): u and w from r itself and a barrier more for the
+// sums. The tip systems are conditioned worse (kappa(P S~) about 2e4): there the
+// pipelined recurrences stop converging near a tolerance of 1e-8 (the cap of
+// 2000 iterations instead of about 300), for 0.96 against 1.01 us per iteration.
+// The loop's time is the latency of its two exchanges through LDS next to the
+// two wavefronts' FMAs, so everything that hangs on the sums (scalars, stopping
+// test) sits where another product is under way; the test is taken after the
+// end: a pass begun after convergence is thrown away. NA: the knots per lane of this
+// wavefront that exist (for some of its lane groups); a wavefront without any
+// only keeps the barriers and the scalars.
+template <int ND, int K, int NA, bool PIPE>
+__device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int lane, int slot,
+                                               const double (&Am)[K][2 * ND], const double (&Ac)[K][2 * ND],
+                                               const double (&Pd)[K][2 * ND], const double (&gam)[K], double (&r)[K],
+                                               double (&lam)[K], double tol, int max_it, bool &capped) {
+  constexpr int NX = 2 * ND, SLOTS = Shape<ND>::SLOTS, G = Shape<ND>::G;
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int p = 0; p < NA; ++p) f(p);
+  };
+  auto publish = [&](double (*buf)[G], const double *x) {
+    each([&](int p) { buf[slot + p * SLOTS + 1][lane] = x[p]; });
+  };
+  auto dinv = [&](const double *x, double *y) {
+    each([&](int p) {
+      y[p] = 0.0;
+      row_dot1<NX>(y[p], x[p], Pd[p]);
+    });
+  };
+  double xl[K], xr[K];   // the neighbours' entries of a published vector
+  auto read = [&](const double (*buf)[G]) {
+    each([&](int p) {
+      xl[p] = buf[slot + p * SLOTS][lane];
+      xr[p] = buf[slot + p * SLOTS + 2][lane];
+    });
+  };
+  auto off = [&](double *y) {   // y = O x
+    each([&](int p) {
+      y[p] = 0.0;
+      row_dot1<NX>(y[p], xl[p], Am[p]);
+      row_dot1<NX>(y[p], xr[p], Ac[p]);
+    });
+  };
+  auto off_sub = [&](double *y) {   // y -= O x
+    each([&](int p) {
+      row_dot1_sub<NX>(y[p], xl[p], Am[p]);
+      row_dot1_sub<NX>(y[p], xr[p], Ac[p]);
+    });
+  };
+  double u[K], w[K], z[K], y[K], v[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) u[p] = w[p] = z[p] = y[p] = v[p] = 0.0;
+  // r = gamma~ - S~ lambda.
+  publish(pb.z, lam);
+  __syncthreads();
+  read(pb.z);
+  off_sub(r);
+  // P gamma~ (for the reference norm) and u = P r, then w = S~ u.
+  __syncthreads();
+  dinv(gam, z);
+  publish(pb.z, z);
+  dinv(r, v);
+  publish(pb.v, v);
+  __syncthreads();
+  read(pb.z);
+  off(y);
+  dinv(y, w);
+  BlockSums sums;
+  double eta = 0.0, unused = 0.0;
+  each([&](int p) { eta += gam[p] * (z[p] - w[p]); });
+  block_sums_put(pb.red, tid, eta, 0.0);
+  read(pb.v);
+  off(y);
+  dinv(y, z);
+  each([&](int p) { u[p] = v[p] - z[p]; });
+  __syncthreads();
+  sums.read(pb.red, tid);
+  sums.get(eta, unused);
+  publish(pb.v, z);
+  __syncthreads();
+  read(pb.v);
+  each([&](int p) { w[p] = r[p]; });
+  off_sub(w);
+  const double stop = tol * tol * eta;
+  double vs[K], vp[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) vs[p] = vp[p] = 0.0;
+  // rg = 1 / gamma_prev and cga = 1 / (gamma_prev alpha_prev) = d_prev /
+  // gamma_prev^2 (d: alpha's divisor) turn beta and alpha into two independent
+  // reciprocals.
+  double rg = 0.0, cga = 0.0;
+  int its = 0;
+  if constexpr (!PIPE) {
+    for (;;) {
+      double pr = 0.0, pw = 0.0;
+      each([&](int p) {
+        pr += r[p] * u[p];
+        pw += w[p] * u[p];
+      });
+      block_sums_put(pb.red, tid, pr, pw);
+      __syncthreads();
+      sums.read(pb.red, tid);
+      double gma, dlt;
+      sums.get(gma, dlt);
+      const double beta = gma * rg;
+      const double d = dlt - gma * gma * cga;
+      rg = rcp_pcg(gma);
+      const double alpha = gma * rcp_pcg(d);
+      cga = d * (rg * rg);
+      capped = gma > stop;
+      if (!__builtin_amdgcn_readfirstlane((int)capped) || its >= max_it) break;
+      each([&](int p) {
+        vs[p] = w[p] + beta * vs[p];
+        r[p] -= alpha * vs[p];
+      });
+      dinv(r, z);
+      publish(pb.z, z);
+      each([&](int p) {
+        vp[p] = u[p] + beta * vp[p];
+        lam[p] += alpha * vp[p];
+      });
+      __syncthreads();
+      read(pb.z);
+      off(y);
+      dinv(y, v);
+      publish(pb.v, v);
+      __syncthreads();
+      read(pb.v);
+      each([&](int p) {
+        u[p] = z[p] - v[p];
+        w[p] = r[p];
+      });
+      off_sub(w);
+      ++its;
+    }
+    return its;
+  }
+  double vz[K], vq[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) vz[p] = vq[p] = 0.0;
+  for (;;) {
+    double pr = 0.0, pw = 0.0;
+    each([&](int p) {
+      pr += r[p] * u[p];
+      pw += w[p] * u[p];
+    });
+    const double part = block_sums_start(tid, pr, pw);
+    dinv(w, z);
+    publish(pb.z, z);
+    block_sums_finish(pb.red, tid, part);
+    __syncthreads();
+    read(pb.z);
+    __builtin_amdgcn_sched_barrier(0);
+    sums.read(pb.red, tid);
+    off(y);
+    double gma, dlt;
+    sums.get(gma, dlt);
+    dinv(y, v);
+    publish(pb.v, v);
+    __syncthreads();
+    read(pb.v);
+    __builtin_amdgcn_sched_barrier(0);
+    const double beta = gma * rg;
+    const double d = dlt - gma * gma * cga;
+    const double rd = rcp_pcg(d);
+    rg = rcp_pcg(gma);
+    const double alpha = gma * rd;
+    cga = d * (rg * rg);
+    each([&](int p) {
+      vq[p] = (z[p] - v[p]) + beta * vq[p];
+      vs[p] = w[p] + beta * vs[p];
+      vp[p] = u[p] + beta * vp[p];
+      r[p] -= alpha * vs[p];
+      u[p] -= alpha * vq[p];
+      y[p] = w[p];
+    });
+    off_sub(y);   // n
+    each([&](int p) {
+      vz[p] = y[p] + beta * vz[p];
+      w[p] -= alpha * vz[p];
+    });
+    capped = gma > stop;
+    if (!__builtin_amdgcn_readfirstlane((int)capped) || its >= max_it) break;
+    each([&](int p) { lam[p] += alpha * vp[p]; });
+    ++its;
+  }
+  return its;
 }
 
 // ---- Exchange between the workgroups (parts) of a split solve. An FP64 value
@@ -1440,6 +1737,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
   using Sh = Shape<ND>;
   constexpr int NX = Sh::NX, NU = Sh::NU, G = Sh::G, SLOTS = Sh::SLOTS;
   constexpr bool kLds = BlockStore<ND, KPT>::kLds;
+  constexpr bool kHalf = half_sweeps<Real, KPT>();
   using SM = Smem<ND, KPT, Real>;
   SM &sm = *reinterpret_cast<SM *>(smem_raw);
   // Only dereferenced by the task-space variant, whose LDS holds it.
@@ -1545,6 +1843,12 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     }
   }
 
+  if constexpr (kHalf) {
+    // (Knots beyond the horizon and the partial sums of wavefronts without
+    // knots are never written in the PCG.)
+    for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += kBlock) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
+    if (tid < 64) sm.pcg.red[tid] = 0.0;
+  }
   // Multipliers of the rows this thread owns (warm start across iterations).
   Real lam[KPT];
 #pragma unroll
@@ -1752,6 +2056,162 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     }
     if (clk) clk[1] = wall_clock64();
 
+    int its = 0;
+    bool capped = false;      // PCG stopped at its iteration limit
+    bool xfail_any = false;   // some part of this solve gave up a wait
+    if constexpr (kHalf) {
+      // ================= 2. Schur rows and diagonal-block inverses, lane = row.
+      double Am[KPT][NX], Ac[KPT][NX];   // rows of O_{k,k-1} = -A_{k-1} Q_{k-1}^-1 and O_{k,k+1} = -Q_k^-1 A_k^T
+      double Pd[KPT][NX];                // row of D_k^-1
+      double gam[KPT], res[KPT], qown[KPT];
+#pragma unroll
+      for (int p = 0; p < KPT; ++p) {
+        const int k = slot + p * SLOTS;
+        double thr[NX];   // row of D_k = theta_{k-1} (Q_0^-1 for k = 0)
+#pragma unroll
+        for (int m = 0; m < NX; ++m) thr[m] = Am[p][m] = Ac[p][m] = Pd[p][m] = 0.0;
+        gam[p] = res[p] = qown[p] = 0.0;
+        if (k < N && lane < NX) {
+          const double *Qik = (k < N - 1) ? sm.Qi : sm.Qni;
+          qown[p] = Qik[lane];
+          if (k == 0) {
+#pragma unroll
+            for (int m = 0; m < NX; ++m) thr[m] = (m == lane) ? sm.Qi[lane] : 0.0;
+            gam[p] = (double)sm.c0[lane] + sm.Qi[lane] * (double)sm.qg[0][lane];
+          } else {
+            const int km = k - 1;
+            const float *A = Ablk(km);
+            const float *B = Bblk(km);
+            double Ar[NX], Br[NU], ArQ[NX], BrR[NU];
+#pragma unroll
+            for (int m = 0; m < NX; ++m) {
+              Ar[m] = (double)A[lane * NX + m];
+              ArQ[m] = Ar[m] * sm.Qi[m];
+              Am[p][m] = -ArQ[m];
+            }
+#pragma unroll
+            for (int m = 0; m < NU; ++m) {
+              Br[m] = (double)B[lane * NU + m];
+              BrR[m] = Br[m] * D.Ri[m];
+            }
+            if constexpr (G == 16) {
+              // Entry (lane, c) of theta: the rows of A_{k-1} and B_{k-1} that
+              // lane c holds, read by row broadcasts.
+#pragma unroll
+              for (int c = 0; c < NX; ++c) thr[c] = (c == lane) ? Qik[lane] : 0.0;
+#pragma unroll
+              for (int m = 0; m < NX; ++m) col_fma<NX>(thr, Ar[m], ArQ[m]);
+#pragma unroll
+              for (int m = 0; m < NU; ++m) col_fma<NX>(thr, Br[m], BrR[m]);
+            } else {
+#pragma unroll
+              for (int c = 0; c < NX; ++c) {
+                double t = (c == lane) ? Qik[lane] : 0.0;
+#pragma unroll
+                for (int m = 0; m < NX; ++m) t += ArQ[m] * (double)A[c * NX + m];
+#pragma unroll
+                for (int m = 0; m < NU; ++m) t += BrR[m] * (double)B[c * NU + m];
+                thr[c] = t;
+              }
+            }
+            double z = (double)sm.e[km][lane] + Qik[lane] * (double)sm.qg[k][lane];
+#pragma unroll
+            for (int m = 0; m < NX; ++m) z -= ArQ[m] * (double)sm.qg[km][m];
+#pragma unroll
+            for (int m = 0; m < NU; ++m) z -= BrR[m] * (double)sm.rg[km][m];
+            gam[p] = z;
+          }
+          if (k < N - 1) {
+            const float *A = Ablk(k);
+#pragma unroll
+            for (int m = 0; m < NX; ++m) Ac[p][m] = -qown[p] * (double)A[m * NX + lane];
+          }
+          // gamma~ - D lambda: the diagonal blocks' only use besides their inverses.
+          res[p] = gam[p];
+          row_dot1_sub<NX>(res[p], lam[p], thr);
+        }
+        // Inverse of the diagonal block: Gauss-Jordan inside the lane group
+        // (the block is SPD, so no pivoting is needed).
+        if (k < N) {
+          if (k == 0) {
+            const double d0 = lane < NX ? 1.0 / sm.Qi[lane] : 0.0;
+#pragma unroll
+            for (int m = 0; m < NX; ++m) Pd[p][m] = (m == lane) ? d0 : 0.0;
+          } else {
+            if constexpr (G == 16 && !TS) {
+              gj_dpp<NX>(thr, lane, std::make_integer_sequence<int, NX>{});
+            } else {
+#pragma unroll
+              for (int pv = 0; pv < NX; ++pv) {
+                if (lane == pv) {
+#pragma unroll
+                  for (int c = 0; c < NX; ++c) sm.piv[slot][c] = thr[c];
+                }
+                wave_sync();
+                double prow[NX];
+#pragma unroll
+                for (int c = 0; c < NX; ++c) prow[c] = sm.piv[slot][c];
+                wave_sync();
+                const double pinv = 1.0 / prow[pv];
+                if (lane == pv) {
+#pragma unroll
+                  for (int c = 0; c < NX; ++c) thr[c] = (c == pv) ? pinv : thr[c] * pinv;
+                } else {
+                  const double f = thr[pv] * pinv;
+#pragma unroll
+                  for (int c = 0; c < NX; ++c) thr[c] = (c == pv) ? -f : thr[c] - f * prow[c];
+                }
+              }
+            }
+#pragma unroll
+            for (int c = 0; c < NX; ++c) Pd[p][c] = lane < NX ? thr[c] : 0.0;
+          }
+        }
+      }
+      if (clk) {
+        clk[2] = wall_clock64();
+        clk[3] = clk[2];
+      }
+      // ================= 3-4. Preconditioned CG.
+      const int max_it = a.pcg_max_iter > 0 ? a.pcg_max_iter : N * NX;
+      const int slot_w = (__builtin_amdgcn_readfirstlane(tid) >> 6) * (64 / G);   // the wavefront's first lane group
+      if (KPT > 1 && slot_w + SLOTS < N)
+        its = pcg_half_sweeps<ND, KPT, KPT, !TS>(sm.pcg, tid, lane, slot, Am, Ac, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
+      else if (slot_w < N)
+        its = pcg_half_sweeps<ND, KPT, 1, !TS>(sm.pcg, tid, lane, slot, Am, Ac, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
+      else
+        its = pcg_half_sweeps<ND, KPT, 0, !TS>(sm.pcg, tid, lane, slot, Am, Ac, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
+      if (clk) clk[4] = wall_clock64();
+      // ================= 5. Step recovery dZ = -G^-1 (g - C^T lambda): with the
+      // scaled columns, dx = -Q^-1 (q - lambda) + Ac lambda_{k+1}.
+      // (z: last read before the barrier that preceded the stopping test.)
+#pragma unroll
+      for (int p = 0; p < KPT; ++p) sm.pcg.z[slot + p * SLOTS + 1][lane] = lam[p];
+      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < KPT; ++p) {
+        const int k = slot + p * SLOTS;
+        if (k < N && lane < NX) {
+          double d = -qown[p] * ((double)sm.qg[k][lane] - lam[p]);
+          row_dot1<NX>(d, sm.pcg.z[k + 2][lane], Ac[p]);
+          const float dx = (float)d;
+          sm.dX[k][lane] = dx;
+          if (!isfinite(dx)) bad_flag = 1;
+          if constexpr (TS) {
+            if (lane < ND) ts.tq[k][lane] = d;
+          }
+          if (lane < NU && k < N - 1) {
+            const float *B = Bblk(k);
+            double su = (double)sm.rg[k][lane];
+#pragma unroll
+            for (int m = 0; m < NX; ++m) su += (double)B[m * NU + lane] * sm.pcg.z[k + 2][m];
+            const float du = (float)(-D.Ri[lane] * su);
+            sm.dU[k][lane] = du;
+            if (!isfinite(du)) bad_flag = 1;
+          }
+        }
+      }
+    } else {
     // ================= 2. Schur complement rows and diagonal-block inverses.
     Real th[kThGlobal ? 1 : KPT][NX];   // row of the diagonal block theta_{k-1} (Q_0^-1 for k = 0)
     // A entries are exact in FP32. With one knot per lane group (FP64
@@ -2356,7 +2816,6 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     for (int p = 0; p < KPT; ++p) eta_ref += gam[p] * Pgam[p];
     const int max_it = a.pcg_max_iter > 0 ? a.pcg_max_iter : N * NX;
     Real gma = 0, stop = 0;
-    int its = 0;
     if constexpr (sizeof(Real) == 4 || TS) {
       // All-FP32 and task-space variants: the standard (Hestenes-Stiefel)
       // arrangement, whose directly computed p^T S~ p tolerates the rounding
@@ -2543,7 +3002,6 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
         ++its;
       }
     }
-    bool xfail_any = false;   // some part of this solve gave up a wait
     if (xon) {
       xlam();
       xon = false;
@@ -2555,7 +3013,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       xsums(f0, f1, f2);
       xfail_any = f0 != 0.0;
     }
-    unsigned status = (gma > stop) ? GATO_ST_PCG_MAXITER : 0u;
+    capped = gma > stop;
     if (clk) clk[4] = wall_clock64();
 
     // ================= 5. Step recovery dZ = -G^-1 (g - C^T lambda).
@@ -2587,6 +3045,8 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
         }
       }
     }
+    }  // !kHalf
+    unsigned status = capped ? GATO_ST_PCG_MAXITER : 0u;
     if constexpr (TS) {
       // Back to x: dx_k = T_k dy_k (joint rows L_k^-T dy), lambda = T_k^-T lambda^.
 #pragma unroll
