@@ -477,8 +477,8 @@ int gato_set_dispatch(gato_batch *b, int mode);
  * four workgroups per solve do not fit the device at once. The parts run the
  * PCG of Sec. III-B (the same Eq. (5) system, preconditioner and stopping
  * rule) together, exchanging halo rows and inner products through device
- * memory at every PCG iteration. With four parts and schur_fp64 = 1 each part
- * forms the LQ data, Schur rows, step and line-search terms of its own 32
+ * memory at every PCG iteration. With schur_fp64 = 1 each part
+ * forms the LQ data, Schur rows, step and line-search terms of its own
  * knots (and of the knots next to them), the merits are summed over the
  * parts, and each part writes its own knots' results; otherwise every part
  * computes the rest of the SQP iteration alike and part 0 writes the results.

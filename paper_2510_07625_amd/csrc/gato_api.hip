@@ -59,7 +59,7 @@ bool dof_supported(int n) { return n == 3 || n == 6 || n == 7; }
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  size_t offA, offB, offD, offT, offAT, total;
+  size_t offA, offB, offD, offT, total;
 };
 
 Layout layout_for(int n, int N) {
@@ -69,8 +69,7 @@ Layout layout_for(int n, int N) {
   l.offB = align256(l.offA + (size_t)(N - 1) * nx * nx * sizeof(float));
   l.offD = align256(l.offB + (size_t)(N - 1) * nx * nu * sizeof(float));
   l.offT = align256(l.offD + (size_t)N * nx * nx * sizeof(float));
-  l.offAT = align256(l.offT + (size_t)N * nx * nx * sizeof(double));
-  l.total = align256(l.offAT + (size_t)(N - 1) * nx * nx * sizeof(float));
+  l.total = align256(l.offT + (size_t)N * nx * nx * sizeof(double));
   return l;
 }
 
@@ -425,7 +424,6 @@ int gato_batch_create(int M, const gato_robot *robots, const gato_problem *probs
     desc[i].offB = (int64_t)l.offB;
     desc[i].offD = (int64_t)l.offD;
     desc[i].offT = (int64_t)l.offT;
-    desc[i].offAT = (int64_t)l.offAT;
     // Long solves (four knots per lane group) can split: a workspace per part
     // and an exchange area.
     const bool can_split = desc[i].kpt == 4 && (!task || prm.schur_fp64);

@@ -31,7 +31,6 @@ struct SolveDesc {
   int64_t ws_off;     // byte offset of this solve's workspace
   int64_t offA, offB, offD, offT;  // byte offsets inside it: A_k, B_k and the inverse
                                    // diagonal blocks (float); Schur diagonal rows (double)
-  int64_t offAT;                   // A_k^T (float), for column reads of A_k
   // Multi-CU split of a long solve (four knots per lane group, FP64 Schur):
   // bytes of one part's workspace (part j at ws_off + j ws_part) and the word
   // offset of the solve's exchange area, or -1 when the solve cannot split.

@@ -14,8 +14,8 @@
 //   3. Stair preconditioner (Eq. (6)): the FP64 variants apply it factored,
 //      P v = D^-1 (v - O D^-1 v) with O the off-diagonal blocks of S~, so only
 //      the rows of D^-1 are kept, and take the S~ product of the result from the
-//      same two half-sweeps (pcg_half_sweeps; four knots per lane group apply
-//      both products in full); the all-FP32 variant's lanes of knot k+1 form
+//      same two half-sweeps (pcg_half_sweeps, pcg_long); the all-FP32 variant's
+//      lanes of knot k+1 form
 //      the off-diagonal block -D_{k+1}^-1 phi_k D_k^-1 once and knot k reads
 //      its transpose. The paper's single grid-wide synchronisation becomes a
 //      workgroup barrier.
@@ -23,15 +23,16 @@
 //      arrangement: the inner products of an iteration are reduced together
 //      and share a barrier with the vector exchange, so an iteration needs two
 //      workgroup barriers. Rows of S~ and P stay in registers; vectors are
-//      exchanged through LDS. (The all-FP32 and task-space variants run the
-//      standard arrangement.)
+//      exchanged through LDS. (The task-space variant and four knots per lane
+//      group take the sums behind a barrier of their own; the all-FP32 variant
+//      runs the standard arrangement.)
 //   5. Step dZ = -G^-1 (g - C^T lambda) (Eq. (4)).
 //   6. Line search (Eqs. (3), (7)): lane (alpha, knot) evaluates one trial
 //      knot; a fixed-order reduction gives each candidate's merit.
 // The Schur rows, gamma~, the block inverses, the PCG vectors and its inner
 // products use Real (double; float for the all-FP32 variant). Dynamics and the
 // line search's trial points use float; the explicit preconditioner blocks of
-// the all-FP32 variant (and the D^-1 rows of four knots per lane group) too.
+// the all-FP32 variant too.
 //
 // Task-space variant (TS): a tip tracking term 1/2 |p(q_k) - pref_k|^2_W per
 // knot makes the joint block of Q_k dense, H_k = diag(Q_q + rho) + J^T W J
@@ -64,20 +65,17 @@ struct Shape {
   static constexpr int NL = ND * (ND + 1) / 2;      // packed Cholesky factor
 };
 
-// QP blocks live in LDS when the workgroup holds at most 32 knots, or one knot
-// per lane group, and in the solve's global workspace otherwise.
-template <int ND, int KPT>
-struct BlockStore {
-  static constexpr int KN = KPT * Shape<ND>::SLOTS;
-  static constexpr bool kLds = (KPT == 1) || (KN <= 32);
-  static constexpr int LB = kLds ? KN : 1;
-};
-
-// The FP64 variants with one or two knots per lane group run the PCG of
-// pcg_half_sweeps (below).
+// The FP64 variants run the PCG of pcg_half_sweeps (below).
 template <class Real, int KPT>
 constexpr bool half_sweeps() {
-  return sizeof(Real) == 8 && KPT <= 2;
+  return sizeof(Real) == 8;
+}
+// Four knots per lane group: the registers hold the D^-1 rows only, the A blocks
+// stay in LDS (their velocity rows in FP32; the joint rows are [I, hI] by
+// construction of the Euler step).
+template <class Real, int KPT>
+constexpr bool long_form() {
+  return half_sweeps<Real, KPT>() && KPT == 4;
 }
 // Its vectors: knot k at row k + 1, zero rows beyond both ends. (K = 0: unused.)
 template <int ND, int K>
@@ -89,13 +87,61 @@ struct PcgBufs {
                                  // [64, 128): written by the lanes without one, never read
 };
 
+// QP blocks live in LDS when the workgroup holds at most 32 knots, or one knot
+// per lane group, and with FP64 Schur rows also at two knots per lane group (but
+// for the 6-7 DoF tip tracking variants, whose factors take that space); in the
+// solve's global workspace otherwise. (7 DoF N = 64, 256 solves: Schur rows 13.6 ->
+// 10.1 us and step 7.7 -> 3.5 us per SQP iteration.)
+template <int ND, int KPT, class Real, bool TS>
+struct BlockStore {
+  static constexpr int KN = KPT * Shape<ND>::SLOTS;
+  static constexpr bool kLds = (KPT == 1) || (KN <= 32) || (KPT == 2 && sizeof(Real) == 8 && !(TS && ND > 3));
+  static constexpr int LB = kLds ? KN : 1;
+};
+
+// LDS that only some phases use: dynamics (qdd, Lf), line search (mp) and PCG
+// (pcg; tv). The long form lets them share their space.
+template <int ND, int KPT, class Real, bool LONG = long_form<Real, KPT>()>
+struct PhaseSmem {
+  using Sh = Shape<ND>;
+  static constexpr int KN = KPT * Sh::SLOTS;
+  static constexpr bool kHalf = half_sweeps<Real, KPT>();
+  static constexpr int KV = kHalf ? 1 : KN;   // vectors of the other arrangements
+  float qdd[KN][8];        // forward dynamics at the knot
+  float Lf[KN][Sh::NL];    // packed Cholesky factor of the inertia matrix
+  PcgBufs<ND, kHalf ? KPT : 0> pcg;
+  union {
+    double mp[kMaxAlpha][KN];  // per-knot merit terms of the step candidates (line search)
+    Real tv[KV][Sh::G];        // exchange inside a lane group (PCG preconditioner)
+  };
+};
 template <int ND, int KPT, class Real>
-struct Smem {
+struct PhaseSmem<ND, KPT, Real, true> {
+  using Sh = Shape<ND>;
+  static constexpr int KN = KPT * Sh::SLOTS;
+  static constexpr int KV = 1;
+  union {
+    struct {
+      float qdd[KN][8];
+      float Lf[KN][Sh::NL];
+      double mp[kMaxAlpha][KN];
+    };
+    PcgBufs<ND, KPT> pcg;
+  };
+  Real tv[1][Sh::G];
+  float Av[KN][ND][2 * ND];   // velocity rows of A_k
+};
+
+template <int ND, int KPT, class Real, bool TS>
+struct Smem : PhaseSmem<ND, KPT, Real> {
   using Sh = Shape<ND>;
   static constexpr int G = Sh::G;
   static constexpr int NX = Sh::NX, NU = Sh::NU;
   static constexpr int KN = KPT * Sh::SLOTS;
-  static constexpr int LB = BlockStore<ND, KPT>::LB;
+  using BS = BlockStore<ND, KPT, Real, TS>;
+  static constexpr bool kHalf = half_sweeps<Real, KPT>();
+  static constexpr int KV = PhaseSmem<ND, KPT, Real>::KV;
+  static constexpr int LP = kHalf ? 1 : BS::LB;
   float X[KN][G];          // iterate
   float U[KN][8];
   float dX[KN][G];         // step
@@ -103,32 +149,23 @@ struct Smem {
   float e[KN][G];          // defects e_k = f(x_k, u_k) - x_{k+1}
   float qg[KN][G];         // state gradients q_k
   float rg[KN][8];         // control gradients r_k
-  float qdd[KN][8];        // forward dynamics at the knot
-  float Lf[KN][Sh::NL];    // packed Cholesky factor of the inertia matrix
-  static constexpr bool kHalf = half_sweeps<Real, KPT>();
-  static constexpr int KV = kHalf ? 1 : KN;   // vectors of the other arrangements
+  double lam[kHalf ? KN : 1][G];   // multipliers between the PCGs
   Real rv[KV][G];          // PCG residual, shared for the preconditioner
   Real gv[KV][G];          // gamma~, shared for the reference norm
   Real pv[KV][G];          // vector shared for the S~ product
   Real sv[KV][G];          // Q_k^-1 times pv
-  PcgBufs<ND, kHalf ? KPT : 0> pcg;
   double piv[Sh::SLOTS][G];  // Gauss-Jordan pivot rows, one per lane group
   double red[2][3][kBlock / 64];  // per-wavefront partial sums
   double mp0[KN];          // per-knot merit terms at the current point
   double Qi[G], Qni[G];    // 1 / (Q + rho), 1 / (Q_N + rho) for the current rho
-  union {
-    double mp[kMaxAlpha][KN];  // per-knot merit terms of the step candidates (line search)
-    Real tv[KV][G];            // exchange inside a lane group (PCG preconditioner)
-  };
   double merit[kMaxAlpha + 1];
   float alpha[kMaxAlpha];
   float xs[G], xg[G], c0[G];
   int bad[2];              // per-iteration flag, indexed by iteration parity
   int xfail, xpad[3];      // split solve: a wait for another part gave up (16 bytes: keeps
                            // the blocks below 16-byte aligned for 128-bit LDS reads)
-  float A[LB][NX * NX];    // A_k
-  float B[LB][NX * NU];    // B_k
-  static constexpr int LP = kHalf ? 1 : LB;
+  float A[BS::LB][NX * NX];    // A_k
+  float B[BS::LB][NX * NU];    // B_k
   float Dinv[LP][NX * NX]; // inverse diagonal blocks of S~
   float Poff[LP][NX * NX]; // P_{k+1,k}
 };
@@ -149,11 +186,11 @@ struct TsSmem {
 
 template <int ND, int KPT, class Real>
 constexpr size_t ts_offset() {
-  return (sizeof(Smem<ND, KPT, Real>) + 15) & ~(size_t)15;
+  return (sizeof(Smem<ND, KPT, Real, true>) + 15) & ~(size_t)15;
 }
 template <int ND, int KPT, class Real, bool TS>
 constexpr size_t smem_bytes() {
-  return TS ? ts_offset<ND, KPT, Real>() + sizeof(TsSmem<ND, KPT>) : sizeof(Smem<ND, KPT, Real>);
+  return TS ? ts_offset<ND, KPT, Real>() + sizeof(TsSmem<ND, KPT>) : sizeof(Smem<ND, KPT, Real, false>);
 }
 
 // Packed lower-triangular storage, row i holding columns 0..i.
@@ -305,6 +342,25 @@ __device__ __forceinline__ void row_dot1_sub_f(double &acc, double x, const floa
   static_assert(NX == 12 || NX == 14, "16-lane groups hold 12 or 14 rows");
   double ta, tb;
   GATO_DOTF("-")
+}
+// The same over the velocity entries m = NX/2..NX-1 only.
+template <int NX>
+__device__ __forceinline__ void row_dot1_vel_f(double &acc, double x, const float *c) {
+  static_assert(NX == 12 || NX == 14, "16-lane groups hold 12 or 14 rows");
+  double ta, tb;
+  if constexpr (NX == 14) {
+    asm volatile("s_nop 1\n\t" GATO_NBF(7, ta, "") GATO_NBF(8, tb, "") GATO_NBF(9, ta, "") GATO_NBF(10, tb, "")
+                 GATO_NBF(11, ta, "") GATO_NBF(12, tb, "") GATO_NBF(13, ta, "")
+                 : "+v"(acc), [ta] "=&v"(ta), [tb] "=&v"(tb)
+                 : [x] "v"(x), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]), [c11] "v"(c[11]),
+                   [c12] "v"(c[12]), [c13] "v"(c[13]));
+  } else {
+    asm volatile("s_nop 1\n\t" GATO_NBF(6, ta, "") GATO_NBF(7, tb, "") GATO_NBF(8, ta, "") GATO_NBF(9, tb, "")
+                 GATO_NBF(10, ta, "") GATO_NBF(11, tb, "")
+                 : "+v"(acc), [ta] "=&v"(ta), [tb] "=&v"(tb)
+                 : [x] "v"(x), [c6] "v"(c[6]), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]),
+                   [c11] "v"(c[11]));
+  }
 }
 #undef GATO_DOTF
 #undef GATO_F12
@@ -533,6 +589,200 @@ struct BlockSums {
   }
 };
 
+// The off-diagonal product at one knot of a lane group: y +- (O x)_k at this
+// lane's row, xl and xr being its entries of x_{k-1} and x_{k+1}.
+// From rows in registers:
+template <int ND, int K>
+struct OffRows {
+  const double (&Am)[K][2 * ND];
+  const double (&Ac)[K][2 * ND];
+  __device__ __forceinline__ void add(int p, double &y, double xl, double xr) const {
+    row_dot1<2 * ND>(y, xl, Am[p]);
+    row_dot1<2 * ND>(y, xr, Ac[p]);
+  }
+  __device__ __forceinline__ void sub(int p, double &y, double xl, double xr) const {
+    row_dot1_sub<2 * ND>(y, xl, Am[p]);
+    row_dot1_sub<2 * ND>(y, xr, Ac[p]);
+  }
+  __device__ __forceinline__ void add_col(int p, double &y, double xr) const { row_dot1<2 * ND>(y, xr, Ac[p]); }
+};
+// From the velocity rows of A in LDS (four knots per lane group): the row of
+// A_{k-1} is read as 2 ND floats, the column of A_k as ND, and the joint rows'
+// [I, hI] costs a lane shift each. FULL (caller-given QP data): A_k as it is,
+// from the workspace (`full`).
+template <int ND, int K, bool FULL>
+struct OffLds {
+  const float (*Av)[ND][2 * ND];
+  const float *full;
+  const double (&qown)[K];   // Q_k^-1 at (lane, lane)
+  double qi;                 // Q^-1 at (lane, lane)
+  double h;
+  int lane, slot, N;
+  __device__ __forceinline__ bool valid(int p) const { return slot + p * Shape<ND>::SLOTS < N && lane < 2 * ND; }
+  // (A_{k-1} Q_{k-1}^-1 x_{k-1}) and (Q_k^-1 A_k^T x_{k+1}) at this lane's row. The
+  // block indexes are clamped where no block is: x is zero there.
+  __device__ __forceinline__ double row(int p, double xl) const {
+    constexpr int NX = 2 * ND;
+    const int km = min(max(slot + p * Shape<ND>::SLOTS - 1, 0), N - 2);
+    const double g = xl * qi;
+    double t = 0.0;
+    if constexpr (FULL) {
+      const float *ar = full + ((size_t)km * NX + min(lane, NX - 1)) * NX;
+#pragma unroll 1
+      for (int m = 0; m < NX; ++m) t += (double)ar[m] * __shfl(g, m, 16);
+      return t;
+    } else {
+      const float *ar = Av[km][lane >= ND && lane < NX ? lane - ND : 0];
+      float c[NX];
+#pragma unroll
+      for (int m = 0; m < NX; ++m) c[m] = ar[m];
+      row_dot1_f<NX>(t, g, c);
+      const double up = dpp<0x100 + ND>(g);   // the entry of lane + ND
+      return lane < ND ? fma(h, up, g) : t;
+    }
+  }
+  __device__ __forceinline__ double col(int p, double xr) const {
+    constexpr int NX = 2 * ND;
+    const int kc = min(slot + p * Shape<ND>::SLOTS, N - 2), l = min(lane, NX - 1);
+    if constexpr (FULL) {
+      double t = 0.0;
+#pragma unroll 1
+      for (int m = 0; m < NX; ++m) t += (double)full[((size_t)kc * NX + m) * NX + l] * __shfl(xr, m, 16);
+      return qown[p] * t;
+    } else {
+      float c[NX];
+#pragma unroll
+      for (int m = 0; m < ND; ++m) c[ND + m] = Av[kc][m][l];
+      const double dn = dpp<0x110 + ND>(xr);   // the entry of lane - ND
+      double t = lane < ND ? xr : h * dn;
+      row_dot1_vel_f<NX>(t, xr, c);
+      return qown[p] * t;
+    }
+  }
+  __device__ __forceinline__ void add(int p, double &y, double xl, double xr) const {
+    const double t = row(p, xl) + col(p, xr);
+    y -= valid(p) ? t : 0.0;
+  }
+  __device__ __forceinline__ void sub(int p, double &y, double xl, double xr) const {
+    const double t = row(p, xl) + col(p, xr);
+    y += valid(p) ? t : 0.0;
+  }
+  __device__ __forceinline__ void add_col(int p, double &y, double xr) const {
+    const double t = col(p, xr);
+    y -= valid(p) ? t : 0.0;
+  }
+};
+
+// One knot's share of the Schur complement (Eq. (5)), lane = row: thr, the row of
+// D_k = theta_{k-1}; gam, the entry of gamma~; res = gam - (D_k lambda_k). first:
+// knot 0, whose block is Q_0^-1. arow(m): the row of A_{k-1}; put(m, x): takes the row of
+// O_{k,k-1}; A, B: the blocks
+// (A only read by 8-lane groups). Lanes 0..NX-1 of the group.
+template <int ND, class Row, class Put>
+__device__ __forceinline__ void schur_knot(int lane, bool first, const Row &arow, const Put &put, const float *A, const float *B,
+                                           const double *Qi, const double *Qik, const double *Ri, const float *c0,
+                                           const float *e, const float *qk, const float *qm, const float *rm,
+                                           double lam, double *thr, double &gam, double &res) {
+  constexpr int NX = 2 * ND, NU = ND;
+  if (first) {
+#pragma unroll
+    for (int m = 0; m < NX; ++m) thr[m] = (m == lane) ? Qi[lane] : 0.0;
+    gam = (double)c0[lane] + Qi[lane] * (double)qk[lane];
+  } else {
+    double Ar[NX], Br[NU], ArQ[NX], BrR[NU];
+#pragma unroll
+    for (int m = 0; m < NX; ++m) {
+      Ar[m] = arow(m);
+      ArQ[m] = Ar[m] * Qi[m];
+      put(m, -ArQ[m]);
+    }
+#pragma unroll
+    for (int m = 0; m < NU; ++m) {
+      Br[m] = (double)B[lane * NU + m];
+      BrR[m] = Br[m] * Ri[m];
+    }
+    if constexpr (Shape<ND>::G == 16) {
+      // Entry (lane, c): the rows of A_{k-1} and B_{k-1} that lane c holds, read
+      // by row broadcasts.
+#pragma unroll
+      for (int c = 0; c < NX; ++c) thr[c] = (c == lane) ? Qik[lane] : 0.0;
+#pragma unroll
+      for (int m = 0; m < NX; ++m) col_fma<NX>(thr, Ar[m], ArQ[m]);
+#pragma unroll
+      for (int m = 0; m < NU; ++m) col_fma<NX>(thr, Br[m], BrR[m]);
+    } else {
+#pragma unroll
+      for (int c = 0; c < NX; ++c) {
+        double t = (c == lane) ? Qik[lane] : 0.0;
+#pragma unroll
+        for (int m = 0; m < NX; ++m) t += ArQ[m] * (double)A[c * NX + m];
+#pragma unroll
+        for (int m = 0; m < NU; ++m) t += BrR[m] * (double)B[c * NU + m];
+        thr[c] = t;
+      }
+    }
+    double z = (double)e[lane] + Qik[lane] * (double)qk[lane];
+#pragma unroll
+    for (int m = 0; m < NX; ++m) z -= ArQ[m] * (double)qm[m];
+#pragma unroll
+    for (int m = 0; m < NU; ++m) z -= BrR[m] * (double)rm[m];
+    gam = z;
+  }
+  res = gam;
+  row_dot1_sub<NX>(res, lam, thr);
+}
+
+// The row of D_k^-1 by Gauss-Jordan elimination inside the lane group (the block
+// is SPD, so no pivoting is needed). DPP: pivot rows by row broadcasts, else
+// through piv (LDS, one row per lane group).
+template <int ND, bool DPP>
+__device__ __forceinline__ void invert_knot(int lane, bool first, const double *Qi, double *thr, double *piv,
+                                            double *Pd) {
+  constexpr int NX = 2 * ND;
+  if (first) {
+    const double d0 = lane < NX ? 1.0 / Qi[lane] : 0.0;
+#pragma unroll
+    for (int m = 0; m < NX; ++m) Pd[m] = (m == lane) ? d0 : 0.0;
+    return;
+  }
+  if constexpr (DPP) {
+    gj_dpp<NX>(thr, lane, std::make_integer_sequence<int, NX>{});
+  } else {
+#pragma unroll
+    for (int pv = 0; pv < NX; ++pv) {
+      if (lane == pv) {
+#pragma unroll
+        for (int c = 0; c < NX; ++c) piv[c] = thr[c];
+      }
+      wave_sync();
+      double prow[NX];
+#pragma unroll
+      for (int c = 0; c < NX; ++c) prow[c] = piv[c];
+      wave_sync();
+      const double pinv = 1.0 / prow[pv];
+      if (lane == pv) {
+#pragma unroll
+        for (int c = 0; c < NX; ++c) thr[c] = (c == pv) ? pinv : thr[c] * pinv;
+      } else {
+        const double f = thr[pv] * pinv;
+#pragma unroll
+        for (int c = 0; c < NX; ++c) thr[c] = (c == pv) ? -f : thr[c] - f * prow[c];
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < NX; ++c) Pd[c] = lane < NX ? thr[c] : 0.0;
+}
+
+// What a solve on one workgroup exchanges with others: nothing.
+struct NoExchange {
+  static constexpr bool on = false;
+  __device__ __forceinline__ void put(const double *) {}
+  __device__ __forceinline__ void get(double *, double *) {}
+  __device__ __forceinline__ void put_sums(double, double) {}
+  __device__ __forceinline__ void get_sums(double &, double &) {}
+};
+
 // Runs the PCG from lam (whose off-diagonal product still has to be taken off
 // the residual r = gamma~ - D lam) and updates lam. Am, Ac, Pd: this lane's rows
 // of the scaled off-diagonal blocks and of D^-1. Returns the iteration count;
@@ -551,10 +801,13 @@ struct BlockSums {
 // test) sits where another product is under way; the test is taken after the
 // end: a pass begun after convergence is thrown away. NA: the knots per lane of this
 // wavefront that exist (for some of its lane groups); a wavefront without any
-// only keeps the barriers and the scalars.
-template <int ND, int K, int NA, bool PIPE>
-__device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int lane, int slot,
-                                               const double (&Am)[K][2 * ND], const double (&Ac)[K][2 * ND],
+// only keeps the barriers and the scalars. A split solve's
+// parts exchange, at each product, their first and last knot's entries and their
+// partial sums (xch; the neighbours' entries stay in the registers of the lane
+// groups next to them).
+template <int ND, int K, int NA, bool PIPE, class Off, class X>
+__device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int lane, int slot, const Off &o,
+                                               X &xch,
                                                const double (&Pd)[K][2 * ND], const double (&gam)[K], double (&r)[K],
                                                double (&lam)[K], double tol, int max_it, bool &capped) {
   constexpr int NX = 2 * ND, SLOTS = Shape<ND>::SLOTS, G = Shape<ND>::G;
@@ -564,6 +817,7 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
   };
   auto publish = [&](double (*buf)[G], const double *x) {
     each([&](int p) { buf[slot + p * SLOTS + 1][lane] = x[p]; });
+    xch.put(x);
   };
   auto dinv = [&](const double *x, double *y) {
     each([&](int p) {
@@ -577,18 +831,17 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
       xl[p] = buf[slot + p * SLOTS][lane];
       xr[p] = buf[slot + p * SLOTS + 2][lane];
     });
+    xch.get(xl, xr);
   };
   auto off = [&](double *y) {   // y = O x
     each([&](int p) {
       y[p] = 0.0;
-      row_dot1<NX>(y[p], xl[p], Am[p]);
-      row_dot1<NX>(y[p], xr[p], Ac[p]);
+      o.add(p, y[p], xl[p], xr[p]);
     });
   };
   auto off_sub = [&](double *y) {   // y -= O x
     each([&](int p) {
-      row_dot1_sub<NX>(y[p], xl[p], Am[p]);
-      row_dot1_sub<NX>(y[p], xr[p], Ac[p]);
+      o.sub(p, y[p], xl[p], xr[p]);
     });
   };
   double u[K], w[K], z[K], y[K], v[K];
@@ -599,27 +852,29 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
   __syncthreads();
   read(pb.z);
   off_sub(r);
-  // P gamma~ (for the reference norm) and u = P r, then w = S~ u.
-  __syncthreads();
+  // P gamma~ (for the reference norm) and u = P r, then w = S~ u. (A buffer is
+  // written again only after a barrier behind its last reads.)
   dinv(gam, z);
-  publish(pb.z, z);
-  dinv(r, v);
-  publish(pb.v, v);
+  publish(pb.v, z);
   __syncthreads();
-  read(pb.z);
+  read(pb.v);
   off(y);
   dinv(y, w);
   BlockSums sums;
   double eta = 0.0, unused = 0.0;
   each([&](int p) { eta += gam[p] * (z[p] - w[p]); });
   block_sums_put(pb.red, tid, eta, 0.0);
-  read(pb.v);
-  off(y);
-  dinv(y, z);
-  each([&](int p) { u[p] = v[p] - z[p]; });
+  dinv(r, v);
+  publish(pb.z, v);
   __syncthreads();
   sums.read(pb.red, tid);
   sums.get(eta, unused);
+  xch.put_sums(eta, 0.0);
+  read(pb.z);
+  xch.get_sums(eta, unused);
+  off(y);
+  dinv(y, z);
+  each([&](int p) { u[p] = v[p] - z[p]; });
   publish(pb.v, z);
   __syncthreads();
   read(pb.v);
@@ -646,6 +901,8 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
       sums.read(pb.red, tid);
       double gma, dlt;
       sums.get(gma, dlt);
+      xch.put_sums(gma, dlt);
+      xch.get_sums(gma, dlt);
       const double beta = gma * rg;
       const double d = dlt - gma * gma * cga;
       rg = rcp_pcg(gma);
@@ -693,17 +950,27 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
     publish(pb.z, z);
     block_sums_finish(pb.red, tid, part);
     __syncthreads();
-    read(pb.z);
-    __builtin_amdgcn_sched_barrier(0);
-    sums.read(pb.red, tid);
-    off(y);
     double gma, dlt;
-    sums.get(gma, dlt);
+    if constexpr (X::on) {
+      // This part's sums leave before the wait for the neighbours' entries.
+      sums.read(pb.red, tid);
+      sums.get(gma, dlt);
+      xch.put_sums(gma, dlt);
+      read(pb.z);
+      off(y);
+    } else {
+      read(pb.z);
+      __builtin_amdgcn_sched_barrier(0);
+      sums.read(pb.red, tid);
+      off(y);
+      sums.get(gma, dlt);
+    }
     dinv(y, v);
     publish(pb.v, v);
     __syncthreads();
     read(pb.v);
     __builtin_amdgcn_sched_barrier(0);
+    xch.get_sums(gma, dlt);
     const double beta = gma * rg;
     const double d = dlt - gma * gma * cga;
     const double rd = rcp_pcg(d);
@@ -729,6 +996,97 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
     ++its;
   }
   return its;
+}
+
+// The same for four knots per lane group, whose registers hold D^-1 and the
+// vectors but not the rows of O (OffLds): one knot at a time between barriers, so
+// that only one knot's entries of A are in registers, and the arrangement with
+// u and w from r (two vectors fewer, one barrier more). na: knots per lane of
+// this wavefront that exist. Bound by the conversions and FMAs of 680 VALU
+// instructions per wavefront and iteration. 6 DoF N = 128, 512 solves: 17.4 us per
+// iteration with all rows read back through L2 (and D^-1 rows in FP32, 5-8% more
+// iterations), 3.3 us; the call 15.1 -> 3.0 ms.
+// The loop's scalars, the same in every lane, are kept in scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+template <int ND, int K, class Off>
+__device__ __forceinline__ int pcg_long(PcgBufs<ND, K> &pb, int tid, int lane, int slot, int na, const Off &o,
+                                        const double (&Pd)[K][2 * ND], const double (&gam)[K], double (&r)[K],
+                                        double (&lam)[K], double tol, int max_it, bool &capped) {
+  constexpr int NX = 2 * ND, SLOTS = Shape<ND>::SLOTS;
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int p = 0; p < K; ++p)
+      if (p < na) f(p, slot + p * SLOTS + 1);
+  };
+  auto dinv = [&](int p, double x) {
+    double y = 0.0;
+    row_dot1<NX>(y, x, Pd[p]);
+    return y;
+  };
+  auto off = [&](int p, const double *const x) {   // (O x) at knot p, x: this lane's entry of the knot's row
+    double y = 0.0;
+    o.add(p, y, x[-Shape<ND>::G], x[Shape<ND>::G]);
+    return y;
+  };
+  BlockSums sums;
+  double u[K], w[K], unused;
+  each([&](int p, int k) { pb.z[k][lane] = lam[p]; });
+  each([&](int p, int k) { pb.v[k][lane] = dinv(p, gam[p]); });
+  __syncthreads();
+  double eta = 0.0;
+  each([&](int p, int k) {
+    r[p] -= off(p, &pb.z[k][lane]);
+    eta += gam[p] * (pb.v[k][lane] - dinv(p, off(p, &pb.v[k][lane])));
+  });
+  block_sums_put(pb.red, tid, eta, 0.0);
+  __syncthreads();
+  sums.read(pb.red, tid);
+  sums.get(eta, unused);
+  const double stop = uniform(tol * tol * eta);
+  double vs[K], vp[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) u[p] = w[p] = vs[p] = vp[p] = 0.0;
+  double rg = 0.0, cga = 0.0, alpha = 0.0, beta = 0.0;
+  // (The first pass only forms u = P r and w = S~ u.)
+  for (int its = -1;;) {
+    each([&](int p, int k) {
+      vs[p] = w[p] + beta * vs[p];
+      vp[p] = u[p] + beta * vp[p];
+      r[p] -= alpha * vs[p];
+      lam[p] += alpha * vp[p];
+      pb.z[k][lane] = dinv(p, r[p]);
+    });
+    ++its;
+    __syncthreads();
+    each([&](int p, int k) {
+      const double v = dinv(p, off(p, &pb.z[k][lane]));
+      pb.v[k][lane] = v;
+      u[p] = pb.z[k][lane] - v;
+    });
+    __syncthreads();
+    double pr = 0.0, pw = 0.0;
+    each([&](int p, int k) {
+      w[p] = r[p] - off(p, &pb.v[k][lane]);
+      pr += r[p] * u[p];
+      pw += w[p] * u[p];
+    });
+    block_sums_put(pb.red, tid, pr, pw);
+    __syncthreads();
+    sums.read(pb.red, tid);
+    double gma, dlt;
+    sums.get(gma, dlt);
+    beta = uniform(gma * rg);
+    const double d = dlt - gma * gma * cga;
+    const double rgm = rcp_pcg(gma);
+    rg = uniform(rgm);
+    alpha = uniform(gma * rcp_pcg(d));
+    cga = uniform(d * (rgm * rgm));
+    capped = gma > stop;
+    if (!__builtin_amdgcn_readfirstlane((int)capped) || its >= max_it) return its;
+  }
 }
 
 // ---- Exchange between the workgroups (parts) of a split solve. An FP64 value
@@ -952,17 +1310,16 @@ __device__ __forceinline__ double tip_lambda(int lane, bool forward, const doubl
 }
 
 // ---- Split long solves, part-local form. A solve of N > 64 knots (6-7 DoF)
-// runs on four workgroups (parts); part j owns knots kf = 32 j .. kl (at most
-// 32, possibly none) and runs the one-knot-per-lane-group layout of a short
-// solve over them, with one halo knot on each side in LDS:
+// runs on four workgroups (parts), or on two when four per solve do not fit the
+// chip; part j owns knots kf = 32 K j .. kl (at most 32 K, possibly none; K = 1 or
+// 2) and runs the layout of K knots per lane group over them, with one halo knot
+// on each side in LDS:
 //   * LQ of its own knots and of the knot left of them (whose A, B, e, q, r the
 //     first own Schur row needs), the defects of its own knots (the knot right
 //     of them is the halo state);
 //   * Schur rows, diagonal-block inverses and PCG rows of its own knots, held
-//     in registers as in a short solve; at both barriers of a PCG iteration
-//     the halo rows of the S~ and preconditioner operands and the partial
-//     inner products travel through device memory (the exchange of the
-//     one-workgroup split form, same words and tags);
+//     in registers as in a short solve; the entries of the knots next to them and
+//     the partial inner products travel through device memory (PartExchange);
 //   * after the PCG: the multipliers of the halo knots, then the step of the
 //     first own knot (the left part's right halo), so that every part holds
 //     the step at its own knots and both halos;
@@ -972,11 +1329,11 @@ __device__ __forceinline__ double tip_lambda(int lane, bool forward, const doubl
 // Part 0 writes the statistics; every part writes its own knots' trajectory
 // and multipliers. The same method as the one-workgroup solve; sums are taken
 // per part first, so results differ from it at rounding level.
-template <int ND>
+template <int ND, int K>
 struct PartSmem {
   using Sh = Shape<ND>;
   static constexpr int G = Sh::G, NX = Sh::NX, NU = Sh::NU, NL = Sh::NL;
-  static constexpr int KS = Sh::SLOTS;   // own knots at most
+  static constexpr int KS = K * Sh::SLOTS;   // own knots at most
   static constexpr int KH = KS + 2;      // with the halo knots: local index li = k - kf + 1
   float X[KH][G];
   float U[KH][8];
@@ -987,12 +1344,8 @@ struct PartSmem {
   float rg[KH][8];
   float qdd[KH][8];
   float Lf[KH][NL];
-  double pv[KH][G];        // operand of S~ (own rows and halos)
-  double sv[KH][G];        // Q_k^-1 times pv
-  double rv[KH][G];        // preconditioner: D_k^-1 times its operand
-  double gv[KH][G];        // Q_k^-1 times rv
-  double piv[KS][G];
-  double red[2][3][kBlock / 64];
+  PcgBufs<ND, K> pcg;      // rows by local index
+  double piv[Sh::SLOTS][G];
   double mp0[KH];
   double Qi[G], Qni[G];
   double mp[kMaxAlpha][KH];
@@ -1024,21 +1377,81 @@ struct PartTsSmem {
 };
 template <int ND>
 constexpr size_t part_ts_offset() {
-  return (sizeof(PartSmem<ND>) + 15) & ~(size_t)15;
+  return (sizeof(PartSmem<ND, 1>) + 15) & ~(size_t)15;
 }
-template <int ND, bool TS>
+template <int ND, int K, bool TS>
 constexpr size_t part_smem_bytes() {
-  return TS ? part_ts_offset<ND>() + sizeof(PartTsSmem<ND>) : sizeof(PartSmem<ND>);
+  return TS ? part_ts_offset<ND>() + sizeof(PartTsSmem<ND>) : sizeof(PartSmem<ND, K>);
 }
 
-template <int ND, bool TS>
+// The larger of the two joint-space part forms.
+template <int ND>
+constexpr size_t long_part_bytes() {
+  return sizeof(PartSmem<ND, 2>) > sizeof(PartSmem<ND, 1>) ? sizeof(PartSmem<ND, 2>) : sizeof(PartSmem<ND, 1>);
+}
+
+// The exchange of one part in the PCG (pcg_half_sweeps; 7 DoF N = 128 on four
+// workgroups 3.0 -> 2.3 us per iteration, 6 DoF N = 100 on two 9.3 -> 2.7): the first and the last
+// own knot's entries of each published vector to the neighbours, theirs into the
+// registers of the lane groups that multiply them, and two sums over the parts.
+// Vectors and sums count their exchanges separately (hx, sx).
+template <int ND, int K>
+struct PartExchange {
+  static constexpr bool on = true;
+  unsigned long long *xb;
+  unsigned epoch;
+  int part, nparts, spin, tid, lane, slot, slot_r, p_r;   // last own knot: lane group slot_r, p_r-th of it
+  bool has_l, has_r;                                      // a neighbour on the left / the right
+  int *xfail;
+  unsigned hx, sx;
+  __device__ __forceinline__ unsigned tag(unsigned e) const { return ((epoch & 0xffffu) << 16) | (e & 0xffffu); }
+  __device__ __forceinline__ unsigned long long *at(int q, unsigned e) const {
+    return xb + (size_t)q * kXPart + (size_t)(e % kXSlots) * kXSlot;
+  }
+  __device__ __forceinline__ void put(const double *x) {
+    if (lane < 2 * ND) {
+      if (has_l && slot == 0) xput(at(part, hx) + 2 * lane, tag(hx), x[0]);
+      if (has_r && slot == slot_r) xput(at(part, hx) + 32 + 2 * lane, tag(hx), p_r == 0 ? x[0] : x[K - 1]);
+    }
+  }
+  __device__ __forceinline__ void get(double *xl, double *xr) {
+    const bool hl = has_l && slot == 0 && lane < 2 * ND, hr = has_r && slot == slot_r && lane < 2 * ND;
+    if (hl || hr) {
+      double v;
+      if (!xget(hl ? at(part - 1, hx) + 32 + 2 * lane : at(part + 1, hx) + 2 * lane, tag(hx), *xfail != 0, spin, v))
+        *xfail = 1;
+      if (hl) xl[0] = v;
+      else if (p_r == 0) xr[0] = v;
+      else xr[K - 1] = v;
+    }
+    ++hx;
+  }
+  __device__ __forceinline__ void put_sums(double a, double b) {
+    if (tid < 2) xput(at(part, sx) + 64 + 2 * tid, tag(sx), tid == 0 ? a : b);
+  }
+  __device__ __forceinline__ void get_sums(double &a, double &b) {
+    const int l = tid & 63;
+    double v = 0.0;
+    if (l < 2 * nparts && !xget(at(l >> 1, sx) + 64 + 2 * (l & 1), tag(sx), *xfail != 0, spin, v)) *xfail = 1;
+    ++sx;
+    a = lane_val(v, 0) + lane_val(v, 2);
+    b = lane_val(v, 1) + lane_val(v, 3);
+    if (nparts == 4) {
+      a += lane_val(v, 4) + lane_val(v, 6);
+      b += lane_val(v, 5) + lane_val(v, 7);
+    }
+  }
+};
+
+template <int ND, int K, bool TS>
 __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs &a, int sid, int part,
                                                                      char *smem_raw) {
   using Sh = Shape<ND>;
   using Real = double;
   constexpr int NX = Sh::NX, NU = Sh::NU, G = Sh::G, SLOTS = Sh::SLOTS;
   static_assert(G == 16, "the part-local split serves 6-7 DoF");
-  using SM = PartSmem<ND>;
+  using SM = PartSmem<ND, K>;
+  static_assert(K == 1 || !TS, "tip tracking splits into four parts");
   SM &sm = *reinterpret_cast<SM *>(smem_raw);
   // Only dereferenced by the task-space form, whose LDS holds it.
   PartTsSmem<ND> &ts = *reinterpret_cast<PartTsSmem<ND> *>(smem_raw + part_ts_offset<ND>());
@@ -1050,10 +1463,11 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
   const int N = D.N;
   const float h = D.dt;
   const int n_alpha = a.n_alpha;
-  const int nparts = kXParts;
+  constexpr int nparts = K == 1 ? kXParts : kXParts / 2;
+  constexpr int KS = K * SLOTS;                              // own knots at most
   const bool writer = part == 0;
-  const int kf = part * SLOTS;                               // own knots kf .. kl
-  const int nloc = max(0, min(SLOTS, N - kf));
+  const int kf = part * KS;                                  // own knots kf .. kl
+  const int nloc = max(0, min(KS, N - kf));
   const int kl = kf + nloc - 1;
   const bool has_l = part > 0 && nloc > 0;                    // a neighbour on the left / the right
   const bool has_r = nloc > 0 && kl + 1 < N;
@@ -1098,24 +1512,28 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
       al = al / a.beta;
     }
   }
-  const bool own0 = slot0 < nloc && lane0 < NX;
-  Real lam = (a.warm && own0) ? (Real)gL[min(kf + slot0 + sh, N - 1) * a.nx_max + lane0] : (Real)0;
-  int redbuf = 0;
-  unsigned xe = 0;
+  double lam[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) {
+    const int i = slot0 + p * SLOTS;
+    lam[p] = (a.warm && i < nloc && lane0 < NX) ? gL[min(kf + i + sh, N - 1) * a.nx_max + lane0] : 0.0;
+  }
   double rho = a.rho[sid];
-  unsigned long long *xb = a.xch + D.xch_off;
-  const int xspin = a.xspin > 0 ? a.xspin : kXSpin;
-  auto xtag = [&](unsigned e) { return ((a.epoch & 0xffffu) << 16) | (e & 0xffffu); };
-  auto xslot = [&](int q, unsigned e) { return xb + (size_t)q * kXPart + (size_t)(e % kXSlots) * kXSlot; };
+  // (Rows without a knot and the partial sums of wavefronts without knots are
+  // never written in the PCG.)
+  for (int t = tid; t < PcgBufs<ND, K>::KH * G; t += kBlock) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
+  if (tid < 64) sm.pcg.red[tid] = 0.0;
+  PartExchange<ND, K> xch{a.xch + D.xch_off, a.epoch, part, nparts, a.xspin > 0 ? a.xspin : kXSpin, tid, lane0, slot0,
+                          (nloc - 1) % SLOTS, nloc > SLOTS ? 1 : 0, has_l, has_r, &sm.xfail, 0u, 0u};
   __syncthreads();
 
   for (int it = 0; it < a.iters; ++it) {
     int lane = lane0, slot = slot0;
     asm volatile("" : "+v"(lane), "+v"(slot));
-    const int k = kf + slot;                 // this group's own knot
-    const int li = slot + 1;
-    const bool own = slot < nloc;
-    if (!a.warm && it > 0) lam = (Real)0;
+    if (!a.warm && it > 0) {
+#pragma unroll
+      for (int p = 0; p < K; ++p) lam[p] = 0.0;
+    }
     if (tid < G) {
       // (Task-space form: the joint block of the rewritten Q_k is the identity.)
       const bool unit = TS && tid < ND;
@@ -1258,275 +1676,81 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
                         sm.e[lg], sm.qg[lg], sm.c0, ts.Jt[lg], ts.pe[lg], succ ? D.We : D.WeN, ts.tq[lg]);
       }
       __syncthreads();
-      if (own) lam = tip_lambda<ND>(lane, true, ts.Lc[li], ts.Li[li], ts.tq[li], lam);
+      if (slot < nloc) lam[0] = tip_lambda<ND>(lane, true, ts.Lc[slot + 1], ts.Li[slot + 1], ts.tq[slot + 1], lam[0]);
     }
     if (clk) clk[1] = wall_clock64();
 
     // ================= 2. Schur rows and diagonal-block inverses of the own knots.
-    Real th[NX], Pdf[NX];
-    double Am[NX], Ac[NX];   // the A_{k-1} row and A_k column, converted once per SQP iteration
-    Real gam = 0, qown = 0;
+    double Am[K][NX], Ac[K][NX], Pd[K][NX], gam[K], res[K], qown[K];
 #pragma unroll
-    for (int m = 0; m < NX; ++m) {
-      th[m] = 0;
-      Am[m] = 0.0;
-      Ac[m] = 0.0;
-      Pdf[m] = 0;
-    }
-    if (own && lane < NX) {
-      const double *Qik = (k < N - 1) ? sm.Qi : sm.Qni;
-      qown = (Real)Qik[lane];
-      if (k == 0) {
+    for (int p = 0; p < K; ++p) {
+      const int i = slot + p * SLOTS, li = i + 1, k = kf + i;
+      double thr[NX];
+      gam[p] = res[p] = qown[p] = 0.0;
 #pragma unroll
-        for (int m = 0; m < NX; ++m) th[m] = (m == lane) ? (Real)sm.Qi[lane] : (Real)0;
-        gam = (Real)sm.c0[lane] + (Real)sm.Qi[lane] * (Real)sm.qg[li][lane];
-      } else {
-        const float *A = sm.A[li - 1];
-        const float *B = sm.B[li - 1];
-        Real ArQ[NX], BrR[NU];
+      for (int m = 0; m < NX; ++m) thr[m] = Am[p][m] = Ac[p][m] = Pd[p][m] = 0.0;
+      if (i < nloc) {
+        const double *Qik = (k < N - 1) ? sm.Qi : sm.Qni;
+        if (lane < NX) {
+          qown[p] = Qik[lane];
+          const float *A = sm.A[li - 1];
+          auto arow = [&](int m) -> double { return (double)A[lane * NX + m]; };
+          auto put = [&](int m, double x) { Am[p][m] = x; };
+          schur_knot<ND>(lane, k == 0, arow, put, A, sm.B[li - 1], sm.Qi, Qik, D.Ri, sm.c0, sm.e[li - 1], sm.qg[li],
+                         sm.qg[li - 1], sm.rg[li - 1], lam[p], thr, gam[p], res[p]);
+          if (k < N - 1) {
+            const float *An = sm.A[li];
 #pragma unroll
-        for (int m = 0; m < NX; ++m) {
-          const float arow = A[lane * NX + m];
-          Am[m] = arow;
-          ArQ[m] = (Real)arow * (Real)sm.Qi[m];
-        }
-#pragma unroll
-        for (int m = 0; m < NU; ++m) BrR[m] = (Real)B[lane * NU + m] * (Real)D.Ri[m];
-#pragma unroll
-        for (int c = 0; c < NX; ++c) {
-          Real t = (c == lane) ? (Real)Qik[lane] : (Real)0;
-#pragma unroll
-          for (int m = 0; m < NX; ++m) t += ArQ[m] * (Real)A[c * NX + m];
-#pragma unroll
-          for (int m = 0; m < NU; ++m) t += BrR[m] * (Real)B[c * NU + m];
-          th[c] = t;
-        }
-        Real z = (Real)sm.e[li - 1][lane] + (Real)Qik[lane] * (Real)sm.qg[li][lane];
-#pragma unroll
-        for (int m = 0; m < NX; ++m) z -= ArQ[m] * (Real)sm.qg[li - 1][m];
-#pragma unroll
-        for (int m = 0; m < NU; ++m) z -= BrR[m] * (Real)sm.rg[li - 1][m];
-        gam = z;
-      }
-      if (k < N - 1) {
-        const float *A = sm.A[li];
-#pragma unroll
-        for (int m = 0; m < NX; ++m) Ac[m] = A[m * NX + lane];
-      }
-    }
-    if (own) {
-      if (k == 0) {
-        const Real d0 = lane < NX ? (Real)1 / (Real)sm.Qi[lane] : (Real)0;
-#pragma unroll
-        for (int m = 0; m < NX; ++m) Pdf[m] = (m == lane) ? d0 : (Real)0;
-      } else {
-        Real row[NX];
-#pragma unroll
-        for (int c = 0; c < NX; ++c) row[c] = th[c];
-#pragma unroll
-        for (int pv = 0; pv < NX; ++pv) {
-          if (lane == pv) {
-#pragma unroll
-            for (int c = 0; c < NX; ++c) sm.piv[slot][c] = row[c];
-          }
-          wave_sync();
-          Real prow[NX];
-#pragma unroll
-          for (int c = 0; c < NX; ++c) prow[c] = sm.piv[slot][c];
-          wave_sync();
-          const Real pinv = (Real)1 / prow[pv];
-          if (lane == pv) {
-#pragma unroll
-            for (int c = 0; c < NX; ++c) row[c] = (c == pv) ? pinv : row[c] * pinv;
-          } else {
-            const Real f = row[pv] * pinv;
-#pragma unroll
-            for (int c = 0; c < NX; ++c) row[c] = (c == pv) ? -f : row[c] - f * prow[c];
+            for (int m = 0; m < NX; ++m) Ac[p][m] = -qown[p] * (double)An[m * NX + lane];
           }
         }
-#pragma unroll
-        for (int c = 0; c < NX; ++c) Pdf[c] = row[c];
+        invert_knot<ND, !TS>(lane, k == 0, sm.Qi, thr, sm.piv[slot], Pd[p]);
       }
     }
-    __syncthreads();
-    if (clk) clk[2] = wall_clock64();
-    if (clk) clk[3] = wall_clock64();
-
-    // ================= 4. PCG (pipelined arrangement), halos and sums through the exchange.
-    const bool rv_ok = own && lane < NX;
-    auto put_row = [&](double left, double right) {   // this group's row to the neighbours (exchange xe)
-      if (lane < NX) {
-        if (has_l && slot == 0) xput(xslot(part, xe) + 2 * lane, xtag(xe), left);
-        if (has_r && slot == nloc - 1) xput(xslot(part, xe) + 32 + 2 * lane, xtag(xe), right);
-      }
-    };
-    // Halo rows of exchange e, for an operand published as vl (the value) and
-    // vr (Q^-1 times it): the left neighbour's last knot sends its vr row,
-    // which lands in vr[0]; the right neighbour's first knot sends its vl row,
-    // which lands in vl[nloc + 1] (the products read vr[li - 1] and
-    // vl[li + 1]). With sums, the three partials of every part summed in part
-    // order.
-    auto get_rows_sums = [&](unsigned e, bool sums, double (*vl)[G], double (*vr)[G], double &s0, double &s1,
-                             double &s2) {
-      const bool dead = sm.xfail != 0;
-      const int l = tid & 63;
-      const bool hl = has_l && slot == 0 && lane < NX;
-      const bool hr = has_r && slot == nloc - 1 && lane < NX;
-      unsigned long long *wh = hl ? xslot(part - 1, e) + 32 + 2 * lane : (hr ? xslot(part + 1, e) + 2 * lane : nullptr);
-      unsigned long long *wsum = (sums && l < 3 * nparts) ? xslot(l / 3, e) + 64 + 2 * (l % 3) : nullptr;
-      double vh = 0.0, v = 0.0;
-      if (wh || wsum) {
-        bool ok;
-        if (wh && wsum) ok = xget2(wh, wsum, xtag(e), dead, xspin, vh, v);
-        else if (wh) ok = xget(wh, xtag(e), dead, xspin, vh);
-        else ok = xget(wsum, xtag(e), dead, xspin, v);
-        if (!ok) sm.xfail = 1;
-      }
-      if (hl) vr[0][lane] = vh;
-      if (hr) vl[nloc + 1][lane] = vh;
-      wave_sync();
-      if (sums) {
-        s0 = (lane_val(v, 0) + lane_val(v, 3)) + (lane_val(v, 6) + lane_val(v, 9));
-        s1 = (lane_val(v, 1) + lane_val(v, 4)) + (lane_val(v, 7) + lane_val(v, 10));
-        s2 = (lane_val(v, 2) + lane_val(v, 5)) + (lane_val(v, 8) + lane_val(v, 11));
-      }
-    };
-    auto halo = [&](double (*vl)[G], double (*vr)[G]) {
-      double d0, d1, d2;
-      get_rows_sums(xe, false, vl, vr, d0, d1, d2);
-      ++xe;
-    };
-    auto share_S = [&](Real v) {
-      if (own) {
-        sm.pv[li][lane] = lane < NX ? v : (Real)0;
-        sm.sv[li][lane] = lane < NX ? qown * v : (Real)0;
-        put_row(v, qown * v);
-      }
-    };
-    auto apply_S = [&](Real v) -> Real {
-      Real d0 = 0, d1 = 0, l0 = 0, l1 = 0, u0 = 0, u1 = 0;
-      row_dot2<NX>(d0, d1, v, th);
-      // Neighbours' entries by row broadcasts: each lane reads its own entry.
-      if (k > 0) row_dot2<NX>(l0, l1, sm.sv[li - 1][lane], Am);
-      if (k < N - 1) row_dot2<NX>(u0, u1, sm.pv[li + 1][lane], Ac);
-      return ((d0 + d1) - (l0 + l1)) - qown * (u0 + u1);
-    };
-    auto dinv = [&](Real x) -> Real {
-      Real acc = 0;
-      row_dot1<NX>(acc, x, Pdf);
-      return acc;
-    };
-    auto prepare_P = [&](Real v) {
-      if (own) {
-        const Real z = dinv(v);
-        sm.rv[li][lane] = lane < NX ? z : (Real)0;
-        sm.gv[li][lane] = lane < NX ? qown * z : (Real)0;
-        put_row(z, qown * z);
-      }
-    };
-    auto finish_P = [&](Real v) -> Real {
-      Real oz = 0;
-      if (k > 0) row_dot1_sub<NX>(oz, sm.gv[li - 1][lane], Am);
-      if (k < N - 1) {
-        Real t = 0;
-        row_dot1<NX>(t, sm.rv[li + 1][lane], Ac);
-        oz -= qown * t;
-      }
-      return dinv(v - oz);
-    };
-
-    Real r, u, w, vm = 0, vn = 0, vz = 0, vq = 0, vs = 0, vp = 0;
-    share_S(lam);
-    __syncthreads();
-    halo(sm.pv, sm.sv);
-    r = rv_ok ? gam - apply_S(lam) : (Real)0;
-    prepare_P(r);
-    __syncthreads();
-    halo(sm.rv, sm.gv);
-    u = rv_ok ? finish_P(r) : (Real)0;
-    __syncthreads();
-    prepare_P(gam);
-    __syncthreads();
-    halo(sm.rv, sm.gv);
-    const Real Pgam = rv_ok ? finish_P(gam) : (Real)0;
-    Real eta_ref = gam * Pgam;
+    if (clk) {
+      clk[2] = wall_clock64();
+      clk[3] = clk[2];
+    }
+    // ================= 3-4. Preconditioned CG, entries and sums through the exchange.
     const int max_it = a.pcg_max_iter > 0 ? a.pcg_max_iter : N * NX;
-    Real gma = 0, stop = 0;
-    int its = 0;
-    share_S(u);
-    __syncthreads();
-    halo(sm.pv, sm.sv);
-    w = rv_ok ? apply_S(u) : (Real)0;
-    eta_ref = wave_sum(eta_ref);
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if ((tid & 63) == 0) sm.red[redbuf][2][wave] = eta_ref;
-    Real rg = 0, cga = 0;
-    for (;;) {
-#pragma unroll
-      for (int m = 0; m < NX; ++m) {
-        asm volatile("" : "+v"(Am[m]), "+v"(Ac[m]));
-        asm volatile("" : "+v"(Pdf[m]));
-      }
-      Real pr = r * u, pwu = w * u;
-      wave_sum2(pr, pwu);
-      if ((tid & 63) == 0) {
-        sm.red[redbuf][0][wave] = pr;
-        sm.red[redbuf][1][wave] = pwu;
-      }
-      prepare_P(w);
-      __syncthreads();
-      gma = pair_tree<kBlock / 64>(sm.red[redbuf][0]);
-      Real dlt = pair_tree<kBlock / 64>(sm.red[redbuf][1]);
-      {
-        const double e0 = (its == 0) ? pair_tree<kBlock / 64>(sm.red[redbuf][2]) : 0.0;
-        if (tid < 3) xput(xslot(part, xe) + 64 + 2 * tid, xtag(xe), tid == 0 ? gma : (tid == 1 ? dlt : e0));
-        double g_, d_, e_;
-        get_rows_sums(xe, true, sm.rv, sm.gv, g_, d_, e_);
-        ++xe;
-        gma = g_;
-        dlt = d_;
-        if (its == 0) stop = (Real)a.pcg_tol * (Real)a.pcg_tol * (Real)e_;
-      }
-      redbuf ^= 1;
-      if (!(gma > stop) || its >= max_it) break;
-      vm = rv_ok ? finish_P(w) : (Real)0;
-      share_S(vm);
-      const Real beta = gma * rg;
-      const Real alpha = div_pcg(gma, dlt - gma * gma * cga);
-      __syncthreads();
-      halo(sm.pv, sm.sv);
-      vn = rv_ok ? apply_S(vm) : (Real)0;
-      vz = vn + beta * vz;
-      vq = vm + beta * vq;
-      vs = w + beta * vs;
-      vp = u + beta * vp;
-      lam += alpha * vp;
-      r -= alpha * vs;
-      u -= alpha * vq;
-      w -= alpha * vz;
-      cga = div_pcg((Real)1, gma * alpha);
-      rg = alpha * cga;
-      ++its;
-    }
-    unsigned status = (gma > stop) ? GATO_ST_PCG_MAXITER : 0u;
+    const int slot_w = (__builtin_amdgcn_readfirstlane(tid) >> 6) * (64 / G);   // the wavefront's first lane group
+    const OffRows<ND, K> off{Am, Ac};
+    bool capped = false;
+    int its;
+    if (K > 1 && slot_w + SLOTS < nloc)
+      its = pcg_half_sweeps<ND, K, K, true>(sm.pcg, tid, lane, slot, off, xch, Pd, gam, res, lam, a.pcg_tol, max_it,
+                                            capped);
+    else if (slot_w < nloc)
+      its = pcg_half_sweeps<ND, K, 1, true>(sm.pcg, tid, lane, slot, off, xch, Pd, gam, res, lam, a.pcg_tol, max_it,
+                                            capped);
+    else
+      its = pcg_half_sweeps<ND, K, 0, true>(sm.pcg, tid, lane, slot, off, xch, Pd, gam, res, lam, a.pcg_tol, max_it,
+                                            capped);
+    unsigned status = capped ? GATO_ST_PCG_MAXITER : 0u;
     if (clk) clk[4] = wall_clock64();
 
     // ================= 5. Step dZ = -G^-1 (g - C^T lambda) at the own knots and the halos.
     // Multipliers of the halo knots first (exchange), then the own steps and the
     // left halo's step (this part holds its LQ data), then the right halo's step
     // from the right part (its first own knot).
-    if (own) {
-      sm.pv[li][lane] = lane < NX ? lam : (Real)0;
-      put_row(lam, lam);
+    // (z: last read before the last barrier of the PCG's loop.)
+    double (*lv)[G] = sm.pcg.z;
+#pragma unroll
+    for (int p = 0; p < K; ++p) lv[slot + p * SLOTS + 1][lane] = lam[p];
+    xch.put(lam);
+    {
+      double xl[K], xr[K];
+      xch.get(xl, xr);
+      if (has_l && slot == 0 && lane < NX) lv[0][lane] = xl[0];
+      if (has_r && slot == xch.slot_r && lane < NX) lv[nloc + 1][lane] = xch.p_r == 0 ? xr[0] : xr[K - 1];
     }
     __syncthreads();
-    halo(sm.pv, sm.pv);
     auto step_at = [&](int lg, int kk, Real lam_own, Real qk) {   // step of knot kk (local lg), row `lane`
       Real sx = (Real)sm.qg[lg][lane] - lam_own;
       if (kk < N - 1) {
         const float *A = sm.A[lg];
 #pragma unroll
-        for (int m = 0; m < NX; ++m) sx += (Real)A[m * NX + lane] * sm.pv[lg + 1][m];
+        for (int m = 0; m < NX; ++m) sx += (Real)A[m * NX + lane] * lv[lg + 1][m];
       }
       const float dx = (float)(-qk * sx);
       sm.dX[lg][lane] = dx;
@@ -1538,14 +1762,18 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
         const float *B = sm.B[lg];
         Real su = (Real)sm.rg[lg][lane];
 #pragma unroll
-        for (int m = 0; m < NX; ++m) su += (Real)B[m * NU + lane] * sm.pv[lg + 1][m];
+        for (int m = 0; m < NX; ++m) su += (Real)B[m * NU + lane] * lv[lg + 1][m];
         const float du = (float)(-(Real)D.Ri[lane] * su);
         sm.dU[lg][lane] = du;
         if (!isfinite(du)) bad_flag = 1;
       }
     };
-    if (own && lane < NX) step_at(li, k, lam, qown);
-    if (has_l && slot == 0 && lane < NX) step_at(0, kf - 1, sm.pv[0][lane], (Real)sm.Qi[lane]);
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      const int i = slot + p * SLOTS;
+      if (i < nloc && lane < NX) step_at(i + 1, kf + i, lam[p], qown[p]);
+    }
+    if (has_l && slot == 0 && lane < NX) step_at(0, kf - 1, lv[0][lane], (Real)sm.Qi[lane]);
     if constexpr (TS) {
       // Back to x: dx_k = T_k dy_k (joint rows L_k^-T dy) at the own knots and
       // the left halo, and lambda = T_k^-T lambda^ at the own knots.
@@ -1564,24 +1792,23 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
           if (!isfinite(dx)) bad_flag = 1;
         }
       };
-      if (own) {
+      if (slot < nloc) {
+        const int li = slot + 1;
         to_x(li);
-        lam = tip_lambda<ND>(lane, false, ts.Lc[li], ts.Li[li], ts.tq[li], lam);
+        lam[0] = tip_lambda<ND>(lane, false, ts.Lc[li], ts.Li[li], ts.tq[li], lam[0]);
       }
       if (has_l && slot == 0) to_x(0);
     }
     __syncthreads();
-    if (own && slot == 0) put_row((double)sm.dX[1][lane], 0.0);
     {
-      // (Only the rows towards the left travel; a part reads its right
-      // neighbour's first step into dX[nloc + 1].)
-      const bool dead = sm.xfail != 0;
-      if (has_r && slot == nloc - 1 && lane < NX) {
-        double v;
-        if (!xget(xslot(part + 1, xe) + 2 * lane, xtag(xe), dead, xspin, v)) sm.xfail = 1;
-        sm.dX[nloc + 1][lane] = (float)v;
-      }
-      ++xe;
+      // The first own knot's step to the left: a part reads its right neighbour's
+      // into dX[nloc + 1].
+      double first[K], xl[K], xr[K];
+#pragma unroll
+      for (int p = 0; p < K; ++p) first[p] = (double)sm.dX[1][lane];
+      xch.put(first);
+      xch.get(xl, xr);
+      if (has_r && slot == xch.slot_r && lane < NX) sm.dX[nloc + 1][lane] = (float)(xch.p_r == 0 ? xr[0] : xr[K - 1]);
     }
     __syncthreads();
     if (clk) clk[5] = wall_clock64();
@@ -1662,16 +1889,16 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
       const int nv = n_alpha + 3;
       if (tid < nv) {
         const double v = tid <= n_alpha ? sm.psum[tid] : (tid == n_alpha + 1 ? (double)bad_flag : (double)sm.xfail);
-        xput(xslot(part, xe) + 64 + 2 * tid, xtag(xe), v);
+        xput(xch.at(part, xch.sx) + 64 + 2 * tid, xch.tag(xch.sx), v);
       }
       const bool dead = sm.xfail != 0;
       if (tid < nv * nparts) {
         const int q = tid / nv, v = tid % nv;
         double x;
-        if (!xget(xslot(q, xe) + 64 + 2 * v, xtag(xe), dead, xspin, x)) sm.xfail = 1;
+        if (!xget(xch.at(q, xch.sx) + 64 + 2 * v, xch.tag(xch.sx), dead, xch.spin, x)) sm.xfail = 1;
         sm.msum[q][v] = x;
       }
-      ++xe;
+      ++xch.sx;
       __syncthreads();
       if (tid <= n_alpha) {
         double m = 0.0;
@@ -1729,16 +1956,21 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     if (j < NX) a.X[xoff + (size_t)kk * a.nx_max + j] = sm.X[lg][j];
     if (kk < N - 1 && j < NU) a.U[uoff + (size_t)kk * a.nu_max + j] = sm.U[lg][j];
   }
-  if (own0) gL[(kf + slot0) * a.nx_max + lane0] = (double)lam;
+#pragma unroll
+  for (int p = 0; p < K; ++p) {
+    const int i = slot0 + p * SLOTS;
+    if (i < nloc && lane0 < NX) gL[(kf + i) * a.nx_max + lane0] = lam[p];
+  }
 }
 
 template <int ND, int KPT, class Real, bool TS = false, bool SPLIT = false>
 __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, int sid, int part, char *smem_raw) {
   using Sh = Shape<ND>;
   constexpr int NX = Sh::NX, NU = Sh::NU, G = Sh::G, SLOTS = Sh::SLOTS;
-  constexpr bool kLds = BlockStore<ND, KPT>::kLds;
+  using BS = BlockStore<ND, KPT, Real, TS>;
   constexpr bool kHalf = half_sweeps<Real, KPT>();
-  using SM = Smem<ND, KPT, Real>;
+  constexpr bool kLong = long_form<Real, KPT>();
+  using SM = Smem<ND, KPT, Real, TS>;
   SM &sm = *reinterpret_cast<SM *>(smem_raw);
   // Only dereferenced by the task-space variant, whose LDS holds it.
   TsSmem<ND, KPT> &ts = *reinterpret_cast<TsSmem<ND, KPT> *>(smem_raw + ts_offset<ND, KPT, Real>());
@@ -1762,13 +1994,13 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
   const int nparts = a.split == 2 ? 2 : kXParts;
   const int psh = nparts == 2 ? 1 : 0;
   const bool split = kSplitOk && a.split && a.mode == kModeSqp && D.xch_off >= 0 && part >= 0 && part < nparts;
-  // Four parts of a long FP64 solve run the part-local form (one knot per
-  // lane group over the part's own knots, FP64 D^-1 rows); two parts, and the
-  // all-FP32 variant, the four-knots-per-group form below.
+  // The parts of a long FP64 solve run the part-local form (one or two knots per
+  // lane group over the part's own knots); those of the all-FP32 variant the
+  // four-knots-per-group form below.
   if constexpr (kSplitOk && sizeof(Real) == 8) {
-    static_assert(sizeof(PartSmem<ND>) <= smem_bytes<ND, KPT, Real, TS>(), "LDS of a part");
-    if (split && a.split == 4 && !a.by_block) {
-      sqp_solve_part<ND, false>(a, sid, part, smem_raw);
+    if (split && !a.by_block) {
+      if (nparts == kXParts) sqp_solve_part<ND, 1, false>(a, sid, part, smem_raw);
+      else sqp_solve_part<ND, 2, false>(a, sid, part, smem_raw);
       return;
     }
   }
@@ -1782,30 +2014,25 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 
   // Block accessors (LDS or the solve's workspace).
   auto Ablk = [&](int k) -> float * {
-    if constexpr (kLds) return sm.A[k];
+    if constexpr (BS::kLds) return sm.A[k];
     else return reinterpret_cast<float *>(ws + D.offA) + (size_t)k * NX * NX;
   };
   auto Bblk = [&](int k) -> float * {
-    if constexpr (kLds) return sm.B[k];
+    if constexpr (BS::kLds) return sm.B[k];
     else return reinterpret_cast<float *>(ws + D.offB) + (size_t)k * NX * NU;
   };
   auto Dblk = [&](int k) -> float * {
-    if constexpr (kLds) return sm.Dinv[k];
+    if constexpr (BS::kLds) return sm.Dinv[k];
     else return reinterpret_cast<float *>(ws + D.offD) + (size_t)k * NX * NX;
   };
   auto Pblk = [&](int k) -> float * {   // explicit preconditioner blocks: kpt == 1 only
-    if constexpr (kLds) return sm.Poff[k];
+    if constexpr (BS::kLds) return sm.Poff[k];
     else return nullptr;
   };
   // Rows of the Schur diagonal blocks, kept in the workspace (read back through
   // L2) when four knots per lane group would not fit them in registers.
   constexpr bool kThGlobal = KPT >= 4;
   auto Tblk = [&](int k) -> Real * { return reinterpret_cast<Real *>(ws + D.offT) + (size_t)k * NX * NX; };
-  // A_k^T in the workspace: the columns of A_k as contiguous rows, for the
-  // kernels that read them back where they are used (one vector load per
-  // four entries instead of a strided load per entry).
-  auto ATblk = [&](int k) -> float * { return reinterpret_cast<float *>(ws + D.offAT) + (size_t)k * NX * NX; };
-  constexpr bool kColsT = KPT >= 4 && sizeof(Real) == 8;
 
   // ---- Stage the iterate and the solve constants in LDS.
   // (With a warm-start shift, knot k starts from the previous knot k + shift,
@@ -1843,7 +2070,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     }
   }
 
-  if constexpr (kHalf) {
+  if constexpr (kHalf && !kLong) {
     // (Knots beyond the horizon and the partial sums of wavefronts without
     // knots are never written in the PCG.)
     for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += kBlock) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
@@ -1857,6 +2084,21 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     lam[p] = (a.warm && a.mode == kModeSqp && k < N && lane0 < NX)
                  ? (Real)gL[min(k + sh, N - 1) * a.nx_max + lane0] : (Real)0;
   }
+  // (FP64 variants: in LDS outside the PCG, which needs the registers of their live
+  // range through the other phases.)
+  auto park = [&]() {
+    if constexpr (kHalf) {
+#pragma unroll
+      for (int p = 0; p < KPT; ++p) sm.lam[slot0 + p * SLOTS][lane0] = lam[p];
+    }
+  };
+  auto unpark = [&]() {
+    if constexpr (kHalf) {
+#pragma unroll
+      for (int p = 0; p < KPT; ++p) lam[p] = sm.lam[slot0 + p * SLOTS][lane0];
+    }
+  };
+  park();
   int redbuf = 0;
   unsigned xe = 0;   // split solve: exchange number (the same sequence in every part)
   // Damping on every Q_k (Sec. IV-C); uniform across the workgroup.
@@ -1873,6 +2115,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     if (!a.warm && it > 0) {
 #pragma unroll
       for (int p = 0; p < KPT; ++p) lam[p] = (Real)0;
+      park();
     }
     // Q^-1 and Q_N^-1 for this iteration's rho (first read after phase 1's barrier).
     // (Task-space variant: the joint block of the rewritten Q_k is the identity.)
@@ -1941,18 +2184,16 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 #pragma unroll
             for (int j = 0; j < ND; ++j) L[i][j] = (j <= i) ? sm.Lf[k][i * (i + 1) / 2 + j] : 0.f;
           chol_solve<ND>(L, col);
-          float *Ak = Ablk(k);
+          if constexpr (kLong) {
 #pragma unroll
-          for (int i = 0; i < ND; ++i) {
-            Ak[i * NX + lane] = (i == lane ? 1.f : 0.f) + (lane == ND + i ? h : 0.f);
-            Ak[(ND + i) * NX + lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
+            for (int i = 0; i < ND; ++i) sm.Av[k][i][lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
           }
-          if constexpr (kColsT) {
-            float *Atk = ATblk(k) + lane * NX;
+          if (!kLong || a.mode == kModeLq) {
+            float *Ak = Ablk(k);
 #pragma unroll
             for (int i = 0; i < ND; ++i) {
-              Atk[i] = (i == lane ? 1.f : 0.f) + (lane == ND + i ? h : 0.f);
-              Atk[ND + i] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
+              Ak[i * NX + lane] = (i == lane ? 1.f : 0.f) + (lane == ND + i ? h : 0.f);
+              Ak[(ND + i) * NX + lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
             }
           }
           if (lane < ND) {
@@ -2016,9 +2257,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       const size_t bo = (size_t)sid * (a.N_max - 1) * a.nx_max * a.nu_max;
       for (int t = tid; t < (N - 1) * NX * NX; t += kBlock) {
         const int k = t / (NX * NX), r = (t / NX) % NX, c = t % NX;
-        const float v = a.inA[ao + ((size_t)k * a.nx_max + r) * a.nx_max + c];
-        Ablk(k)[r * NX + c] = v;
-        if constexpr (kColsT) ATblk(k)[c * NX + r] = v;
+        Ablk(k)[r * NX + c] = a.inA[ao + ((size_t)k * a.nx_max + r) * a.nx_max + c];
       }
       for (int t = tid; t < (N - 1) * NX * NU; t += kBlock) {
         const int k = t / (NX * NU), r = (t / NU) % NX, c = t % NU;
@@ -2038,6 +2277,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     // The other parity's flag was last read before the previous iteration's
     // closing barrier; clear it for the next iteration.
     if (tid == 0) sm.bad[(it + 1) & 1] = 0;
+    unpark();
     if constexpr (TS) {
       for (int t = tid; t < N; t += kBlock) sm.mp0[t] += ts.mt[t];
       // Rewrite the QP in y_k = T_k^-1 x_k, and the warm-start multipliers
@@ -2061,130 +2301,88 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     bool xfail_any = false;   // some part of this solve gave up a wait
     if constexpr (kHalf) {
       // ================= 2. Schur rows and diagonal-block inverses, lane = row.
-      double Am[KPT][NX], Ac[KPT][NX];   // rows of O_{k,k-1} = -A_{k-1} Q_{k-1}^-1 and O_{k,k+1} = -Q_k^-1 A_k^T
-      double Pd[KPT][NX];                // row of D_k^-1
+      double Am[kLong ? 1 : KPT][NX], Ac[kLong ? 1 : KPT][NX];   // rows of O_{k,k-1} and O_{k,k+1} (OffRows)
+      double Pd[KPT][NX];                                        // row of D_k^-1
       double gam[KPT], res[KPT], qown[KPT];
+      // The A blocks of the long form as they are (caller-given QP data only).
+      const float *full = kLong && a.mode == kModeKkt ? Ablk(0) : nullptr;
+      if constexpr (kLong) {
+        for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += kBlock) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
+        if (tid < 64) sm.pcg.red[tid] = 0.0;
+      }
 #pragma unroll
       for (int p = 0; p < KPT; ++p) {
         const int k = slot + p * SLOTS;
-        double thr[NX];   // row of D_k = theta_{k-1} (Q_0^-1 for k = 0)
-#pragma unroll
-        for (int m = 0; m < NX; ++m) thr[m] = Am[p][m] = Ac[p][m] = Pd[p][m] = 0.0;
+        double thr[NX];
         gam[p] = res[p] = qown[p] = 0.0;
-        if (k < N && lane < NX) {
-          const double *Qik = (k < N - 1) ? sm.Qi : sm.Qni;
-          qown[p] = Qik[lane];
-          if (k == 0) {
 #pragma unroll
-            for (int m = 0; m < NX; ++m) thr[m] = (m == lane) ? sm.Qi[lane] : 0.0;
-            gam[p] = (double)sm.c0[lane] + sm.Qi[lane] * (double)sm.qg[0][lane];
-          } else {
-            const int km = k - 1;
-            const float *A = Ablk(km);
-            const float *B = Bblk(km);
-            double Ar[NX], Br[NU], ArQ[NX], BrR[NU];
-#pragma unroll
-            for (int m = 0; m < NX; ++m) {
-              Ar[m] = (double)A[lane * NX + m];
-              ArQ[m] = Ar[m] * sm.Qi[m];
-              Am[p][m] = -ArQ[m];
-            }
-#pragma unroll
-            for (int m = 0; m < NU; ++m) {
-              Br[m] = (double)B[lane * NU + m];
-              BrR[m] = Br[m] * D.Ri[m];
-            }
-            if constexpr (G == 16) {
-              // Entry (lane, c) of theta: the rows of A_{k-1} and B_{k-1} that
-              // lane c holds, read by row broadcasts.
-#pragma unroll
-              for (int c = 0; c < NX; ++c) thr[c] = (c == lane) ? Qik[lane] : 0.0;
-#pragma unroll
-              for (int m = 0; m < NX; ++m) col_fma<NX>(thr, Ar[m], ArQ[m]);
-#pragma unroll
-              for (int m = 0; m < NU; ++m) col_fma<NX>(thr, Br[m], BrR[m]);
-            } else {
-#pragma unroll
-              for (int c = 0; c < NX; ++c) {
-                double t = (c == lane) ? Qik[lane] : 0.0;
-#pragma unroll
-                for (int m = 0; m < NX; ++m) t += ArQ[m] * (double)A[c * NX + m];
-#pragma unroll
-                for (int m = 0; m < NU; ++m) t += BrR[m] * (double)B[c * NU + m];
-                thr[c] = t;
-              }
-            }
-            double z = (double)sm.e[km][lane] + Qik[lane] * (double)sm.qg[k][lane];
-#pragma unroll
-            for (int m = 0; m < NX; ++m) z -= ArQ[m] * (double)sm.qg[km][m];
-#pragma unroll
-            for (int m = 0; m < NU; ++m) z -= BrR[m] * (double)sm.rg[km][m];
-            gam[p] = z;
-          }
-          if (k < N - 1) {
-            const float *A = Ablk(k);
-#pragma unroll
-            for (int m = 0; m < NX; ++m) Ac[p][m] = -qown[p] * (double)A[m * NX + lane];
-          }
-          // gamma~ - D lambda: the diagonal blocks' only use besides their inverses.
-          res[p] = gam[p];
-          row_dot1_sub<NX>(res[p], lam[p], thr);
+        for (int m = 0; m < NX; ++m) {
+          thr[m] = Pd[p][m] = 0.0;
+          if constexpr (!kLong) Am[p][m] = Ac[p][m] = 0.0;
         }
-        // Inverse of the diagonal block: Gauss-Jordan inside the lane group
-        // (the block is SPD, so no pivoting is needed).
         if (k < N) {
-          if (k == 0) {
-            const double d0 = lane < NX ? 1.0 / sm.Qi[lane] : 0.0;
+          const double *Qik = (k < N - 1) ? sm.Qi : sm.Qni;
+          if (lane < NX) {
+            const int km = max(k - 1, 0);
+            auto arow = [&](int m) -> double {
+              if constexpr (kLong) {
+                if (!full)
+                  return lane < ND ? (m == lane ? 1.0 : 0.0) + (m == lane + ND ? (double)h : 0.0)
+                                   : (double)sm.Av[km][max(lane - ND, 0)][m];
+              }
+              return (double)Ablk(km)[lane * NX + m];
+            };
+            qown[p] = Qik[lane];
+            auto put = [&](int m, double x) {
+              if constexpr (!kLong) Am[p][m] = x;
+            };
+            schur_knot<ND>(lane, k == 0, arow, put, Ablk(km), Bblk(km), sm.Qi, Qik, D.Ri, sm.c0, sm.e[km], sm.qg[k],
+                           sm.qg[km], sm.rg[km], lam[p], thr, gam[p], res[p]);
+            if constexpr (!kLong) {
+              if (k < N - 1) {
+                const float *A = Ablk(k);
 #pragma unroll
-            for (int m = 0; m < NX; ++m) Pd[p][m] = (m == lane) ? d0 : 0.0;
-          } else {
-            if constexpr (G == 16 && !TS) {
-              gj_dpp<NX>(thr, lane, std::make_integer_sequence<int, NX>{});
-            } else {
-#pragma unroll
-              for (int pv = 0; pv < NX; ++pv) {
-                if (lane == pv) {
-#pragma unroll
-                  for (int c = 0; c < NX; ++c) sm.piv[slot][c] = thr[c];
-                }
-                wave_sync();
-                double prow[NX];
-#pragma unroll
-                for (int c = 0; c < NX; ++c) prow[c] = sm.piv[slot][c];
-                wave_sync();
-                const double pinv = 1.0 / prow[pv];
-                if (lane == pv) {
-#pragma unroll
-                  for (int c = 0; c < NX; ++c) thr[c] = (c == pv) ? pinv : thr[c] * pinv;
-                } else {
-                  const double f = thr[pv] * pinv;
-#pragma unroll
-                  for (int c = 0; c < NX; ++c) thr[c] = (c == pv) ? -f : thr[c] - f * prow[c];
-                }
+                for (int m = 0; m < NX; ++m) Ac[p][m] = -qown[p] * (double)A[m * NX + lane];
               }
             }
-#pragma unroll
-            for (int c = 0; c < NX; ++c) Pd[p][c] = lane < NX ? thr[c] : 0.0;
           }
+          invert_knot<ND, G == 16 && !TS>(lane, k == 0, sm.Qi, thr, sm.piv[slot], Pd[p]);
         }
       }
+      if constexpr (kLong) __syncthreads();   // (the PCG's buffers are clear)
       if (clk) {
         clk[2] = wall_clock64();
         clk[3] = clk[2];
       }
-      // ================= 3-4. Preconditioned CG.
+      // ================= 3-5. Preconditioned CG, then the step dZ = -G^-1 (g - C^T
+      // lambda): with the scaled columns, dx = -Q^-1 (q - lambda) + O_{k,k+1} lambda_{k+1}.
       const int max_it = a.pcg_max_iter > 0 ? a.pcg_max_iter : N * NX;
       const int slot_w = (__builtin_amdgcn_readfirstlane(tid) >> 6) * (64 / G);   // the wavefront's first lane group
-      if (KPT > 1 && slot_w + SLOTS < N)
-        its = pcg_half_sweeps<ND, KPT, KPT, !TS>(sm.pcg, tid, lane, slot, Am, Ac, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
-      else if (slot_w < N)
-        its = pcg_half_sweeps<ND, KPT, 1, !TS>(sm.pcg, tid, lane, slot, Am, Ac, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
-      else
-        its = pcg_half_sweeps<ND, KPT, 0, !TS>(sm.pcg, tid, lane, slot, Am, Ac, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
+      NoExchange none;
+      auto off = [&]() {
+        if constexpr (kLong)
+          return OffLds<ND, KPT, false>{sm.Av, nullptr, qown, lane < NX ? sm.Qi[lane] : 0.0, (double)h, lane, slot, N};
+        else
+          return OffRows<ND, KPT>{Am, Ac};
+      }();
+      const OffLds<ND, KPT, true> off_full{nullptr, full, qown, lane < NX ? sm.Qi[lane] : 0.0, 0.0, lane, slot, N};
+      if constexpr (kLong) {
+        int na = 0;
+        for (int p = 0; p < KPT; ++p) na += slot_w + p * SLOTS < N ? 1 : 0;
+        its = full ? pcg_long<ND, KPT>(sm.pcg, tid, lane, slot, na, off_full, Pd, gam, res, lam, a.pcg_tol, max_it, capped)
+                   : pcg_long<ND, KPT>(sm.pcg, tid, lane, slot, na, off, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
+      } else if (KPT > 1 && slot_w + SLOTS < N) {
+        its = pcg_half_sweeps<ND, KPT, KPT, !TS>(sm.pcg, tid, lane, slot, off, none, Pd, gam, res, lam, a.pcg_tol,
+                                                 max_it, capped);
+      } else if (slot_w < N) {
+        its = pcg_half_sweeps<ND, KPT, 1, !TS>(sm.pcg, tid, lane, slot, off, none, Pd, gam, res, lam, a.pcg_tol,
+                                               max_it, capped);
+      } else {
+        its = pcg_half_sweeps<ND, KPT, 0, !TS>(sm.pcg, tid, lane, slot, off, none, Pd, gam, res, lam, a.pcg_tol,
+                                               max_it, capped);
+      }
       if (clk) clk[4] = wall_clock64();
-      // ================= 5. Step recovery dZ = -G^-1 (g - C^T lambda): with the
-      // scaled columns, dx = -Q^-1 (q - lambda) + Ac lambda_{k+1}.
-      // (z: last read before the barrier that preceded the stopping test.)
+      // (z: last read before the last barrier of the PCG's loop.)
 #pragma unroll
       for (int p = 0; p < KPT; ++p) sm.pcg.z[slot + p * SLOTS + 1][lane] = lam[p];
       __syncthreads();
@@ -2193,7 +2391,8 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
         const int k = slot + p * SLOTS;
         if (k < N && lane < NX) {
           double d = -qown[p] * ((double)sm.qg[k][lane] - lam[p]);
-          row_dot1<NX>(d, sm.pcg.z[k + 2][lane], Ac[p]);
+          if (kLong && full) off_full.add_col(p, d, sm.pcg.z[k + 2][lane]);
+          else off.add_col(p, d, sm.pcg.z[k + 2][lane]);
           const float dx = (float)d;
           sm.dX[k][lane] = dx;
           if (!isfinite(dx)) bad_flag = 1;
@@ -2214,32 +2413,8 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     } else {
     // ================= 2. Schur complement rows and diagonal-block inverses.
     Real th[kThGlobal ? 1 : KPT][NX];   // row of the diagonal block theta_{k-1} (Q_0^-1 for k = 0)
-    // A entries are exact in FP32. With one knot per lane group (FP64
-    // variant) the rows are held converted to FP64, once per SQP iteration:
-    // the PCG loop then converts nothing (28 conversions fewer per iteration)
-    // and, since its two products would otherwise keep FP64 copies of the
-    // FP32 rows live across the second barrier, holds fewer registers too
-    // (spills 88 -> 20 B/lane, 12% off the headline call). Elsewhere they
-    // are kept in FP32 (converted to Real at use), which halves their
-    // register footprint. With four knots per lane group (FP64 variant) the
-    // rows are read back from the A blocks in the workspace where they are
-    // used (as the Schur rows are), which frees 112 registers per lane; the
-    // FP32 variant has the room.
-    constexpr bool kRowsGlobal = KPT >= 4 && sizeof(Real) == 8;
-    static_assert(kRowsGlobal == kColsT, "column reads of A_k need its transposed copy");
-    constexpr int KR = kRowsGlobal ? 1 : KPT;
-    constexpr bool kRealA = (KPT == 1) && sizeof(Real) == 8 && !TS;
-    using AT = std::conditional_t<kRealA, double, float>;
-    AT Am[KR][NX];     // row `lane` of A_{k-1}: S~_{k,k-1} = -A_{k-1} Q_{k-1}^-1
-    AT Ac[KR][NX];     // column `lane` of A_k: S~_{k,k+1} = -Q_k^-1 A_k^T
-    auto am = [&](int p, int m) -> AT {
-      if constexpr (kRowsGlobal) return Ablk(slot + p * SLOTS - 1)[lane * NX + m];
-      else return Am[p][m];
-    };
-    auto ac = [&](int p, int m) -> AT {
-      if constexpr (kRowsGlobal) return ATblk(slot + p * SLOTS)[lane * NX + m];
-      else return Ac[p][m];
-    };
+    Real Am[KPT][NX];   // row `lane` of A_{k-1}: S~_{k,k-1} = -A_{k-1} Q_{k-1}^-1
+    Real Ac[KPT][NX];   // column `lane` of A_k: S~_{k,k+1} = -Q_k^-1 A_k^T
     Real gam[KPT];
     Real qown[KPT];       // Q_k^-1 at (lane, lane)
     Real Pd[KPT][NX];     // row of the inverse diagonal block (preconditioner)
@@ -2251,10 +2426,8 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 #pragma unroll
       for (int m = 0; m < NX; ++m) {
         thr[m] = 0;
-        if constexpr (!kRowsGlobal) {
-          Am[p][m] = 0.f;
-          Ac[p][m] = 0.f;
-        }
+        Am[p][m] = 0.f;
+        Ac[p][m] = 0.f;
         Pd[p][m] = 0;
       }
       gam[p] = 0;
@@ -2274,33 +2447,19 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 #pragma unroll
           for (int m = 0; m < NX; ++m) {
             const float arow = A[lane * NX + m];
-            if constexpr (!kRowsGlobal) Am[p][m] = arow;
+            Am[p][m] = arow;
             ArQ[m] = (Real)arow * (Real)sm.Qi[m];
           }
 #pragma unroll
           for (int m = 0; m < NU; ++m) BrR[m] = (Real)B[lane * NU + m] * (Real)D.Ri[m];
-          if constexpr (sizeof(Real) == 8 && G == 16 && !kRowsGlobal) {
-            // Entry (lane, c) of theta: the rows of A_{k-1} and B_{k-1} that
-            // lane c holds, read by row broadcasts (same terms, same order).
-            double Br[NU];
 #pragma unroll
-            for (int m = 0; m < NU; ++m) Br[m] = (double)B[lane * NU + m];
+          for (int c = 0; c < NX; ++c) {
+            Real t = (c == lane) ? (Real)Qik[lane] : (Real)0;
 #pragma unroll
-            for (int c = 0; c < NX; ++c) thr[c] = (c == lane) ? (Real)Qik[lane] : (Real)0;
+            for (int m = 0; m < NX; ++m) t += ArQ[m] * (Real)A[c * NX + m];
 #pragma unroll
-            for (int m = 0; m < NX; ++m) col_fma<NX>(thr, (double)Am[p][m], ArQ[m]);
-#pragma unroll
-            for (int m = 0; m < NU; ++m) col_fma<NX>(thr, Br[m], BrR[m]);
-          } else {
-#pragma unroll
-            for (int c = 0; c < NX; ++c) {
-              Real t = (c == lane) ? (Real)Qik[lane] : (Real)0;
-#pragma unroll
-              for (int m = 0; m < NX; ++m) t += ArQ[m] * (Real)A[c * NX + m];
-#pragma unroll
-              for (int m = 0; m < NU; ++m) t += BrR[m] * (Real)B[c * NU + m];
-              thr[c] = t;
-            }
+            for (int m = 0; m < NU; ++m) t += BrR[m] * (Real)B[c * NU + m];
+            thr[c] = t;
           }
           Real z = (Real)sm.e[km][lane] + (Real)Qik[lane] * (Real)sm.qg[k][lane];
 #pragma unroll
@@ -2309,12 +2468,10 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
           for (int m = 0; m < NU; ++m) z -= BrR[m] * (Real)sm.rg[km][m];
           gam[p] = z;
         }
-        if constexpr (!kRowsGlobal) {
-          if (k < N - 1) {
-            const float *A = Ablk(k);
+        if (k < N - 1) {
+          const float *A = Ablk(k);
 #pragma unroll
-            for (int m = 0; m < NX; ++m) Ac[p][m] = A[m * NX + lane];
-          }
+          for (int m = 0; m < NX; ++m) Ac[p][m] = A[m * NX + lane];
         }
       }
       // Inverse of the diagonal block: Gauss-Jordan inside the lane group
@@ -2389,30 +2546,17 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     //   P_{k,k-1} = -D_k^-1 phi_{k-1} D_{k-1}^-1,  phi_{k-1} = -A_{k-1} Q_{k-1}^-1,
     // keep it, and publish it so that knot k-1 can read its column. Either
     // form is a fixed linear operator, as the pipelined recurrences require.
-    // With kFactP (the FP64 variants, and several knots per lane group where
-    // registers are short) the off-diagonal blocks are not formed:
+    // With kFactP (several knots per lane group, where registers are short, and
+    // tip tracking) the off-diagonal blocks are not formed:
     // P w = D^-1 (w - O D^-1 w), with O the off-diagonal blocks of S~ that the
     // S~ product already holds.
-    constexpr bool kFactP = KPT > 1 || TS || sizeof(Real) == 8;
+    constexpr bool kFactP = KPT > 1 || TS;
     constexpr int KP = kFactP ? 1 : KPT;
-    // D^-1 rows: held in Real for one and two knots per lane group (FP64) and
-    // for the task-space variant, in FP32 (converted at use) otherwise.
-    // Rounding D^-1 to FP32 perturbs the preconditioner's smallest directions
-    // (P ~ S~^-1), which slows PCG and moves where a truncated PCG stops: on
-    // the headline batch the slowest solve needs 9% more iterations, at
-    // N = 64 up to 13% more, and the iterate at the stop then departs from the
-    // FP64 method's by up to 1e-3 after three SQP iterations (1e-5 with FP64
-    // rows); on the far worse conditioned task-space systems 30-80% more. With
-    // two knots per group the FP64 rows cost spills (288 against 208 B/lane,
-    // 22% per PCG iteration); with four they would cost far more, and long
-    // solves split across workgroups instead.
-    constexpr bool kRealP = TS || (KPT <= 2 && sizeof(Real) == 8);
-    using PT = std::conditional_t<kRealP, Real, float>;
-    PT Pm[KP][NX], Pp[KP][NX], Pdf[KPT][NX];
+    Real Pm[KP][NX], Pp[KP][NX], Pdf[KPT][NX];
 #pragma unroll
     for (int p = 0; p < KPT; ++p) {
 #pragma unroll
-      for (int m = 0; m < NX; ++m) Pdf[p][m] = kRealP ? (PT)Pd[p][m] : (PT)(float)Pd[p][m];
+      for (int m = 0; m < NX; ++m) Pdf[p][m] = Pd[p][m];
     }
     if constexpr (!kFactP) {
 #pragma unroll
@@ -2459,17 +2603,9 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     }  // !kFactP
 
     if (clk) clk[3] = wall_clock64();
-    // ================= 4. PCG on S~ lambda = gamma~, pipelined arrangement.
-    // Per iteration, with u = P r, w = S~ u kept by recurrence:
-    //   gamma = (r, u), delta = (w, u)         [partials published with w]
-    //   m = P w, n = S~ m
-    //   beta = gamma / gamma_prev, alpha = gamma / (delta - beta gamma / alpha_prev)
-    //   z = n + beta z, q = m + beta q, s = w + beta s, p = u + beta p
-    //   lambda += alpha p, r -= alpha s, u -= alpha q, w -= alpha z
-    // In exact arithmetic this is the standard PCG iteration; the reduction of
-    // an iteration shares a workgroup barrier with the vector exchange, so an
-    // iteration needs two barriers and the scalar divisions overlap the
-    // matrix-vector products.
+    // ================= 4. PCG on S~ lambda = gamma~: the standard (Hestenes-Stiefel)
+    // arrangement, whose directly computed p^T S~ p tolerates the rounding of FP32
+    // vectors.
     // Split solve: this part's rows only, until the multipliers are gathered.
     bool xon = split;
     auto own = [&](int p) { return !xon || (p >> psh) == part; };
@@ -2593,87 +2729,46 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     // chains are short and independent; with more knots the extra accumulators
     // would cost registers (spills), so the odd columns fold into the even sums.
     constexpr bool kSplit = (KPT == 1);
-    // The knot's own block-row products (the diagonal block of S~ and the
-    // D^-1 products of the preconditioner) by DPP row broadcasts from the
-    // registers (16-lane groups, FP64); the neighbours' blocks still read the
-    // neighbours' published vectors from LDS.
-    constexpr bool kDpp = (G == 16) && (sizeof(Real) == 8);
-    // own: this lane's entry of the vector the product multiplies (the value
-    // share_S published in pv).
-    auto apply_S = [&](int p, Real own) -> Real {
+    auto apply_S = [&](int p) -> Real {
       const int k = slot + p * SLOTS;
       if constexpr (kSplit) {
         Real d0 = 0, d1 = 0, l0 = 0, l1 = 0, u0 = 0, u1 = 0;
-        if constexpr (kDpp) {
-          row_dot2<NX>(d0, d1, own, th[p]);
-        } else {
+#pragma unroll
+        for (int m = 0; m < NX; m += 2) {
+          d0 += th[p][m] * sm.pv[k][m];
+          d1 += th[p][m + 1] * sm.pv[k][m + 1];
+        }
+        if (k > 0) {
 #pragma unroll
           for (int m = 0; m < NX; m += 2) {
-            d0 += th[p][m] * sm.pv[k][m];
-            d1 += th[p][m + 1] * sm.pv[k][m + 1];
+            l0 += Am[p][m] * sm.sv[k - 1][m];
+            l1 += Am[p][m + 1] * sm.sv[k - 1][m + 1];
           }
         }
-        if constexpr (kDpp) {
-          // The neighbours' entries by row broadcasts too: each lane reads
-          // its own entry of the neighbour's vector (one LDS read, not 14).
-          if (k > 0) {
-            double c[NX];
+        if (k < N - 1) {
 #pragma unroll
-            for (int m = 0; m < NX; ++m) c[m] = (double)Am[p][m];
-            row_dot2<NX>(l0, l1, sm.sv[k - 1][lane], c);
-          }
-          if (k < N - 1) {
-            double c[NX];
-#pragma unroll
-            for (int m = 0; m < NX; ++m) c[m] = (double)Ac[p][m];
-            row_dot2<NX>(u0, u1, sm.pv[k + 1][lane], c);
-          }
-        } else {
-          if (k > 0) {
-#pragma unroll
-            for (int m = 0; m < NX; m += 2) {
-              l0 += (Real)Am[p][m] * sm.sv[k - 1][m];
-              l1 += (Real)Am[p][m + 1] * sm.sv[k - 1][m + 1];
-            }
-          }
-          if (k < N - 1) {
-#pragma unroll
-            for (int m = 0; m < NX; m += 2) {
-              u0 += (Real)Ac[p][m] * sm.pv[k + 1][m];
-              u1 += (Real)Ac[p][m + 1] * sm.pv[k + 1][m + 1];
-            }
+          for (int m = 0; m < NX; m += 2) {
+            u0 += Ac[p][m] * sm.pv[k + 1][m];
+            u1 += Ac[p][m + 1] * sm.pv[k + 1][m + 1];
           }
         }
         return ((d0 + d1) - (l0 + l1)) - qown[p] * (u0 + u1);
       } else {
         Real acc = 0;
-        if constexpr (kDpp && !kThGlobal) {
-          row_dot1<NX>(acc, own, th[p]);
-        } else {
 #pragma unroll
-          for (int m = 0; m < NX; ++m) {
-            if constexpr (kThGlobal) acc += Tblk(k)[lane * NX + m] * sm.pv[k][m];
-            else acc += th[p][m] * sm.pv[k][m];
-          }
+        for (int m = 0; m < NX; ++m) {
+          if constexpr (kThGlobal) acc += Tblk(k)[lane * NX + m] * sm.pv[k][m];
+          else acc += th[p][m] * sm.pv[k][m];
         }
-        if constexpr (kDpp && !kRowsGlobal && !kRealA) {
-          if (k > 0) row_dot1_sub_f<NX>(acc, sm.sv[k - 1][lane], Am[p]);
-          if (k < N - 1) {
-            Real t = 0;
-            row_dot1_f<NX>(t, sm.pv[k + 1][lane], Ac[p]);
-            acc -= qown[p] * t;
-          }
-        } else {
-          if (k > 0) {
+        if (k > 0) {
 #pragma unroll
-            for (int m = 0; m < NX; ++m) acc -= (Real)am(p, m) * sm.sv[k - 1][m];
-          }
-          if (k < N - 1) {
-            Real t = 0;
+          for (int m = 0; m < NX; ++m) acc -= Am[p][m] * sm.sv[k - 1][m];
+        }
+        if (k < N - 1) {
+          Real t = 0;
 #pragma unroll
-            for (int m = 0; m < NX; ++m) t += (Real)ac(p, m) * sm.pv[k + 1][m];
-            acc -= qown[p] * t;
-          }
+          for (int m = 0; m < NX; ++m) t += Ac[p][m] * sm.pv[k + 1][m];
+          acc -= qown[p] * t;
         }
         return acc;
       }
@@ -2714,18 +2809,11 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     auto group_dinv = [&](int p, Real x) -> Real {   // row `lane` of D_k^-1 times the group's x
       const int k = slot + p * SLOTS;
       Real acc = 0;
-      if constexpr (kDpp) {
-        double c[NX];
+      sm.tv[k][lane] = (lane < NX) ? x : (Real)0;
+      wave_sync();
 #pragma unroll
-        for (int m = 0; m < NX; ++m) c[m] = (double)Pdf[p][m];
-        row_dot1<NX>(acc, x, c);
-      } else {
-        sm.tv[k][lane] = (lane < NX) ? x : (Real)0;
-        wave_sync();
-#pragma unroll
-        for (int m = 0; m < NX; ++m) acc += (Real)Pdf[p][m] * sm.tv[k][m];
-        wave_sync();
-      }
+      for (int m = 0; m < NX; ++m) acc += Pdf[p][m] * sm.tv[k][m];
+      wave_sync();
       return acc;
     };
     auto prepare_P = [&](const Real *vals) {
@@ -2743,51 +2831,27 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     auto finish_P = [&](int p, Real v) -> Real {
       const int k = slot + p * SLOTS;
       Real oz = 0;   // (O z)_k at row `lane`
-      if constexpr (kDpp && KPT == 2 && !kRealA) {
-        if (k > 0) row_dot1_sub_f<NX>(oz, sm.gv[k - 1][lane], Am[p]);
-        if (k < N - 1) {
-          Real t = 0;
-          row_dot1_f<NX>(t, sm.rv[k + 1][lane], Ac[p]);
-          oz -= qown[p] * t;
-        }
-      } else if constexpr (kDpp && KPT == 1) {
-        if (k > 0) {
-          double c[NX];
+      if (k > 0) {
 #pragma unroll
-          for (int m = 0; m < NX; ++m) c[m] = (double)am(p, m);
-          row_dot1_sub<NX>(oz, sm.gv[k - 1][lane], c);
-        }
-        if (k < N - 1) {
-          Real t = 0;
-          double c[NX];
+        for (int m = 0; m < NX; ++m) oz -= Am[p][m] * sm.gv[k - 1][m];
+      }
+      if (k < N - 1) {
+        Real t = 0;
 #pragma unroll
-          for (int m = 0; m < NX; ++m) c[m] = (double)ac(p, m);
-          row_dot1<NX>(t, sm.rv[k + 1][lane], c);
-          oz -= qown[p] * t;
-        }
-      } else {
-        if (k > 0) {
-#pragma unroll
-          for (int m = 0; m < NX; ++m) oz -= (Real)am(p, m) * sm.gv[k - 1][m];
-        }
-        if (k < N - 1) {
-          Real t = 0;
-#pragma unroll
-          for (int m = 0; m < NX; ++m) t += (Real)ac(p, m) * sm.rv[k + 1][m];
-          oz -= qown[p] * t;
-        }
+        for (int m = 0; m < NX; ++m) t += Ac[p][m] * sm.rv[k + 1][m];
+        oz -= qown[p] * t;
       }
       return group_dinv(p, v - oz);
     };
     auto row_valid = [&](int p) { return (slot + p * SLOTS) < N && lane < NX && own(p); };
 
     // r = gamma~ - S~ lambda, u = P r, w = S~ u; eta_ref = gamma~^T P gamma~.
-    Real r[KPT], u[KPT], w[KPT], vm[KPT], vn[KPT], vz[KPT], vq[KPT], vs[KPT], vp[KPT];
+    Real r[KPT], u[KPT], w[KPT], vp[KPT];
     share_S(lam);
     __syncthreads();
     if (xon) xhalo(sm.pv, sm.sv);
 #pragma unroll
-    for (int p = 0; p < KPT; ++p) r[p] = row_valid(p) ? gam[p] - apply_S(p, lam[p]) : (Real)0;
+    for (int p = 0; p < KPT; ++p) r[p] = row_valid(p) ? gam[p] - apply_S(p) : (Real)0;
     Real Pgam[KPT];   // P gamma~, for the reference norm
     if constexpr (kFactP) {
       prepare_P(r);
@@ -2816,14 +2880,8 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     for (int p = 0; p < KPT; ++p) eta_ref += gam[p] * Pgam[p];
     const int max_it = a.pcg_max_iter > 0 ? a.pcg_max_iter : N * NX;
     Real gma = 0, stop = 0;
-    if constexpr (sizeof(Real) == 4 || TS) {
-      // All-FP32 and task-space variants: the standard (Hestenes-Stiefel)
-      // arrangement, whose directly computed p^T S~ p tolerates the rounding
-      // of FP32 vectors, and which on the worse-conditioned task-space systems
-      // is also the faster one (fewer live registers than the pipelined
-      // recurrences next to the variant's own state).
-      // Acc: the accumulation type of the inner products (double when FP64
-      // accumulation is asked for, and for FP64 vectors).
+    {
+      // Acc: the accumulation type of the inner products.
       auto run = [&](auto tag) {
         using Acc = decltype(tag);
         Acc sums[3] = {0, 0, 0};
@@ -2849,7 +2907,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
           Acc pw[1] = {0};
 #pragma unroll
           for (int p = 0; p < KPT; ++p) {
-            w[p] = row_valid(p) ? apply_S(p, vp[p]) : (Real)0;
+            w[p] = row_valid(p) ? apply_S(p) : (Real)0;
             pw[0] += (Acc)vp[p] * (Acc)w[p];
           }
           block_sum<1>(sm.red, redbuf, pw);
@@ -2891,116 +2949,8 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
         gma = (g > stop_a) ? (Real)1 : (Real)0;
         stop = 0;
       };
-      if constexpr (sizeof(Real) == 8) run(double{});
-      else if (a.fp64_dot) run(double{});
+      if (a.fp64_dot) run(double{});
       else run(float{});
-    } else {
-      share_S(u);
-      __syncthreads();
-      if (xon) xhalo(sm.pv, sm.sv);
-#pragma unroll
-      for (int p = 0; p < KPT; ++p) {
-        w[p] = row_valid(p) ? apply_S(p, u[p]) : (Real)0;
-        vz[p] = vq[p] = vs[p] = vp[p] = 0;
-      }
-      eta_ref = wave_sum(eta_ref);
-      const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: kept in a scalar register
-      if ((tid & 63) == 0) sm.red[redbuf][2][wave] = eta_ref;
-      // rg = 1 / gamma_prev and c = 1 / (gamma_prev alpha_prev), formed in the
-      // previous iteration off the critical path, turn
-      //   beta = gamma / gamma_prev, alpha = gamma / (delta - beta gamma / alpha_prev)
-      // into beta = gamma rg, alpha = gamma / (delta - gamma^2 c): one division.
-      Real rg = 0, cga = 0;
-      for (;;) {
-        // Keep the matrix rows as they are across iterations (stops the
-        // compiler from hoisting conversions of FP32 rows and doubling their
-        // registers).
-#pragma unroll
-        for (int p = 0; p < KPT; ++p)
-#pragma unroll
-          for (int m = 0; m < NX; ++m) {
-            if constexpr (!kRowsGlobal) asm volatile("" : "+v"(Am[p][m]), "+v"(Ac[p][m]));
-            asm volatile("" : "+v"(Pdf[p][m]));
-          }
-        if constexpr (!kFactP) {
-#pragma unroll
-          for (int p = 0; p < KPT; ++p)
-#pragma unroll
-            for (int m = 0; m < NX; ++m) asm volatile("" : "+v"(Pm[p][m]), "+v"(Pp[p][m]));
-        }
-        // Publish w for m = P w together with the partial inner products.
-        Real pr = 0, pwu = 0;
-#pragma unroll
-        for (int p = 0; p < KPT; ++p) {
-          pr += r[p] * u[p];
-          pwu += w[p] * u[p];
-        }
-        if constexpr (kSplit) {
-          wave_sum2(pr, pwu);
-        } else {
-          pr = wave_sum(pr);
-          pwu = wave_sum(pwu);
-        }
-        if ((tid & 63) == 0) {
-          sm.red[redbuf][0][wave] = pr;
-          sm.red[redbuf][1][wave] = pwu;
-        }
-        if constexpr (kFactP) prepare_P(w);
-        else share_P(w, sm.rv);
-        __syncthreads();
-        // Pairwise tree over the per-wavefront partials (fixed order).
-        gma = pair_tree<kBlock / 64>(sm.red[redbuf][0]);
-        Real dlt = pair_tree<kBlock / 64>(sm.red[redbuf][1]);
-        if (xon) {
-          // Halo rows for finish_P and this part's inner products out; the
-          // neighbours' rows and the sums over the parts in.
-          const double e0 = (its == 0) ? pair_tree<kBlock / 64>(sm.red[redbuf][2]) : 0.0;
-          xsum_put(xe, gma, dlt, e0);
-          double g_, d_, e_;
-          xhalo_sum_get(xe, true, sm.rv, sm.gv, g_, d_, e_);
-          ++xe;
-          gma = (Real)g_;
-          dlt = (Real)d_;
-          if (its == 0) stop = (Real)a.pcg_tol * (Real)a.pcg_tol * (Real)e_;
-        } else if (its == 0) {
-          stop = (Real)a.pcg_tol * (Real)a.pcg_tol * pair_tree<kBlock / 64>(sm.red[redbuf][2]);
-        }
-        redbuf ^= 1;
-        if (!(gma > stop) || its >= max_it) break;
-#pragma unroll
-        for (int p = 0; p < KPT; ++p) {
-          if constexpr (kFactP) vm[p] = row_valid(p) ? finish_P(p, w[p]) : (Real)0;
-          else vm[p] = row_valid(p) ? apply_P(p, sm.rv) : (Real)0;
-        }
-        share_S(vm);
-        // (kpt > 1: the quotients in the textbook order, whose operands are
-        // short-lived; rg and cga then hold gamma_prev and alpha_prev.)
-        const Real beta = kSplit ? gma * rg : ((its == 0) ? (Real)0 : div_pcg(gma, rg));
-        const Real alpha = kSplit ? div_pcg(gma, dlt - gma * gma * cga)
-                                  : ((its == 0) ? div_pcg(gma, dlt) : div_pcg(gma, dlt - div_pcg(beta * gma, cga)));
-        __syncthreads();
-        if (xon) xhalo(sm.pv, sm.sv);
-#pragma unroll
-        for (int p = 0; p < KPT; ++p) {
-          vn[p] = row_valid(p) ? apply_S(p, vm[p]) : (Real)0;
-          vz[p] = vn[p] + beta * vz[p];
-          vq[p] = vm[p] + beta * vq[p];
-          vs[p] = w[p] + beta * vs[p];
-          vp[p] = u[p] + beta * vp[p];
-          lam[p] += alpha * vp[p];
-          r[p] -= alpha * vs[p];
-          u[p] -= alpha * vq[p];
-          w[p] -= alpha * vz[p];
-        }
-        if constexpr (kSplit) {
-          cga = div_pcg((Real)1, gma * alpha);
-          rg = alpha * cga;
-        } else {
-          rg = gma;
-          cga = alpha;
-        }
-        ++its;
-      }
     }
     if (xon) {
       xlam();
@@ -3026,7 +2976,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
         Real sx = (Real)sm.qg[k][lane] - lam[p];
         if (k < N - 1) {
 #pragma unroll
-          for (int m = 0; m < NX; ++m) sx += (Real)ac(p, m) * sm.pv[k + 1][m];
+          for (int m = 0; m < NX; ++m) sx += Ac[p][m] * sm.pv[k + 1][m];
         }
         const float dx = (float)(-qown[p] * sx);
         sm.dX[k][lane] = dx;
@@ -3094,6 +3044,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       if (tid == 0 && a.outits) a.outits[sid] = its;
       return;
     }
+    park();
     __syncthreads();
     if (clk) clk[5] = wall_clock64();
 
@@ -3196,6 +3147,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 
   // ---- Write back the iterate, the warm-start multipliers and the adapted damping.
   const int lane = lane0, slot = slot0;
+  unpark();
   if (a.mode == kModeSqp && writer) {
     if (a.rho_adapt && tid == 0) a.rho[sid] = rho;
     const size_t rxo = (size_t)blockIdx.x * a.N_max * a.nx_max;
@@ -3221,8 +3173,11 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 
 template <int ND, int KPT, class Real, bool TS = false, bool SPLIT = false>
 __global__ __launch_bounds__(kBlock) void sqp_kernel(KArgs a) {
-  static_assert(smem_bytes<ND, KPT, Real, TS>() <= 160 * 1024, "LDS of one workgroup exceeds 160 KB");
-  __shared__ __align__(16) char smem[smem_bytes<ND, KPT, Real, TS>()];
+  constexpr size_t kOne = smem_bytes<ND, KPT, Real, TS>();
+  constexpr size_t kPart = SPLIT && sizeof(Real) == 8 ? long_part_bytes<ND>() : 0;
+  constexpr size_t kBytes = kOne > kPart ? kOne : kPart;
+  static_assert(kBytes <= 160 * 1024, "LDS of one workgroup exceeds 160 KB");
+  __shared__ __align__(16) char smem[kBytes];
   int sid = a.order ? a.order[blockIdx.x] : a.sid_base + (int)blockIdx.x;
   int part = 0;
   if constexpr (SPLIT) {
@@ -3242,14 +3197,14 @@ __global__ __launch_bounds__(kBlock) void sqp_kernel(KArgs a) {
 // two knots per 8-lane group already cover the maximum horizon; the
 // task-space variant is compiled for one and two knots per group, and its
 // long solves (6-7 DoF, N > 64) run only split, in the part-local form.)
-template <class Real, bool TS>
+template <class Real, bool TS, bool SPLIT>
 constexpr size_t mixed_smem_bytes() {
-  size_t m = 0;
+  size_t m = SPLIT && !TS && sizeof(Real) == 8 ? long_part_bytes<7>() : 0;
   const size_t s[] = {smem_bytes<3, 1, Real, TS>(), smem_bytes<3, 2, Real, TS>(),
                       smem_bytes<6, 1, Real, TS>(), smem_bytes<6, 2, Real, TS>(),
-                      TS ? part_smem_bytes<6, true>() : smem_bytes<6, 4, Real, false>(),
+                      TS ? part_smem_bytes<6, 1, true>() : smem_bytes<6, 4, Real, false>(),
                       smem_bytes<7, 1, Real, TS>(), smem_bytes<7, 2, Real, TS>(),
-                      TS ? part_smem_bytes<7, true>() : smem_bytes<7, 4, Real, false>()};
+                      TS ? part_smem_bytes<7, 1, true>() : smem_bytes<7, 4, Real, false>()};
   for (size_t v : s) m = v > m ? v : m;
   return m;
 }
@@ -3262,8 +3217,8 @@ __device__ __forceinline__ bool task_split_ok(const KArgs &a, const SolveDesc &D
 
 template <class Real, bool TS = false, bool SPLIT = false>
 __global__ __launch_bounds__(kBlock) void sqp_mixed_kernel(KArgs a) {
-  static_assert(mixed_smem_bytes<Real, TS>() <= 160 * 1024, "LDS of one workgroup exceeds 160 KB");
-  __shared__ __align__(16) char smem[mixed_smem_bytes<Real, TS>()];
+  static_assert(mixed_smem_bytes<Real, TS, SPLIT>() <= 160 * 1024, "LDS of one workgroup exceeds 160 KB");
+  __shared__ __align__(16) char smem[mixed_smem_bytes<Real, TS, SPLIT>()];
   int sid = a.order ? a.order[blockIdx.x] : a.sid_base + (int)blockIdx.x;
   int part = 0;
   if constexpr (SPLIT) {
@@ -3284,13 +3239,13 @@ __global__ __launch_bounds__(kBlock) void sqp_mixed_kernel(KArgs a) {
     case 6 * 8 + 4:
       if constexpr (!TS) sqp_solve<6, 4, Real, false, SPLIT>(a, sid, part, smem);
       else if constexpr (SPLIT && sizeof(Real) == 8) {
-        if (task_split_ok(a, D, part)) sqp_solve_part<6, true>(a, sid, part, smem);
+        if (task_split_ok(a, D, part)) sqp_solve_part<6, 1, true>(a, sid, part, smem);
       }
       break;
     case 7 * 8 + 4:
       if constexpr (!TS) sqp_solve<7, 4, Real, false, SPLIT>(a, sid, part, smem);
       else if constexpr (SPLIT && sizeof(Real) == 8) {
-        if (task_split_ok(a, D, part)) sqp_solve_part<7, true>(a, sid, part, smem);
+        if (task_split_ok(a, D, part)) sqp_solve_part<7, 1, true>(a, sid, part, smem);
       }
       break;
     default: break;  // the host only builds the shapes above

@@ -20,14 +20,22 @@ import paper_2510_07625_amd as g  # noqa: E402
 
 
 # 6-7 DoF: 4 knots per wavefront, 32 per pass over the lane groups, one or two
-# passes; 3 DoF: 8 per wavefront, 64 per pass.
-@pytest.mark.parametrize("n,N", [(7, 4), (7, 5), (6, 17), (7, 29), (7, 31), (6, 36), (7, 37), (7, 63), (3, 7), (3, 9),
-                                 (3, 63), (3, 65), (3, 73), (3, 128)])
-def test_kkt_at_the_edges_of_the_split(n, N):
-    print(f"[gpu-case] pcg edges n={n} N={N}", flush=True)
+# passes, up to four passes with the A blocks' velocity rows in LDS; 3 DoF: 8 per
+# wavefront, 64 per pass. general: joint rows of A other than [I, hI], which the
+# Euler step never gives but a caller may.
+@pytest.mark.parametrize("n,N,general", [(7, 4, 0), (7, 5, 0), (6, 17, 0), (7, 29, 0), (7, 31, 0), (6, 36, 0),
+                                         (7, 37, 0), (7, 63, 0), (3, 7, 0), (3, 9, 0), (3, 63, 0), (3, 65, 0),
+                                         (3, 73, 0), (3, 128, 0), (7, 65, 0), (6, 97, 0), (6, 101, 0), (7, 127, 0),
+                                         (6, 128, 0), (7, 32, 1), (6, 64, 1), (7, 100, 1), (6, 128, 1)])
+def test_kkt_at_the_edges_of_the_split(n, N, general):
+    print(f"[gpu-case] pcg edges n={n} N={N} general={general}", flush=True)
     solves = [w.chain_solve(51, i, n=n, N=N) for i in range(3)]
     nx = 2 * n
     data = [oracle.lq(s, s.X0, s.U0) for s in solves]
+    if general:
+        rng = np.random.default_rng(5)
+        for d in data:
+            d["A"] = d["A"] + 0.02 * rng.normal(size=d["A"].shape)
     f32 = [{k: np.asarray(v, np.float32).astype(np.float64) for k, v in d.items()} for d in data]
     b = g.Batch.from_solves(solves, g.Params(pcg_tol=1e-9))
     dev = lambda k: torch.from_numpy(np.stack([c[k] for c in f32]).astype(np.float32)).cuda()
