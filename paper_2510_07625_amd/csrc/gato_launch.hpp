@@ -48,7 +48,7 @@ inline hipError_t cooperative_fits(const void *f, int grid) {
   return cap >= grid ? hipSuccess : hipErrorCooperativeLaunchTooLarge;
 }
 
-// Launches the closed-loop plant step (RK4, one thread per instance).
+// Launches the closed-loop plant step (RK4, one 16-lane group per instance).
 hipError_t launch_plant(const PlantArgs &a, hipStream_t s);
 
 // Fills n doubles with v.
