@@ -780,6 +780,7 @@ struct NoExchange {
   __device__ __forceinline__ void put(const double *) {}
   __device__ __forceinline__ void get(double *, double *) {}
   __device__ __forceinline__ void put_sums(double, double) {}
+  __device__ __forceinline__ void wait_sums() {}
   __device__ __forceinline__ void get_sums(double &, double &) {}
 };
 
@@ -871,13 +872,14 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
   sums.get(eta, unused);
   xch.put_sums(eta, 0.0);
   read(pb.z);
-  xch.get_sums(eta, unused);
   off(y);
   dinv(y, z);
   each([&](int p) { u[p] = v[p] - z[p]; });
   publish(pb.v, z);
+  xch.wait_sums();
   __syncthreads();
   read(pb.v);
+  xch.get_sums(eta, unused);
   each([&](int p) { w[p] = r[p]; });
   off_sub(w);
   const double stop = tol * tol * eta;
@@ -890,6 +892,7 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
   double rg = 0.0, cga = 0.0;
   int its = 0;
   if constexpr (!PIPE) {
+    static_assert(!X::on, "the parts of a split solve run the pipelined loop");
     for (;;) {
       double pr = 0.0, pw = 0.0;
       each([&](int p) {
@@ -901,8 +904,6 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
       sums.read(pb.red, tid);
       double gma, dlt;
       sums.get(gma, dlt);
-      xch.put_sums(gma, dlt);
-      xch.get_sums(gma, dlt);
       const double beta = gma * rg;
       const double d = dlt - gma * gma * cga;
       rg = rcp_pcg(gma);
@@ -967,6 +968,7 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
     }
     dinv(y, v);
     publish(pb.v, v);
+    xch.wait_sums();
     __syncthreads();
     read(pb.v);
     __builtin_amdgcn_sched_barrier(0);
@@ -1345,6 +1347,7 @@ struct PartSmem {
   float qdd[KH][8];
   float Lf[KH][NL];
   PcgBufs<ND, K> pcg;      // rows by local index
+  double total[2];         // sums over the parts
   double piv[Sh::SLOTS][G];
   double mp0[KH];
   double Qi[G], Qni[G];
@@ -1391,7 +1394,9 @@ constexpr size_t long_part_bytes() {
 }
 
 // The exchange of one part in the PCG (pcg_half_sweeps; 7 DoF N = 128 on four
-// workgroups 3.0 -> 2.3 us per iteration, 6 DoF N = 100 on two 9.3 -> 2.7): the first and the last
+// workgroups 3.0 -> 1.95 us per iteration, 6 DoF N = 100 on two 9.3 -> 2.35; tip
+// tracking N = 128 3.2 -> 2.4; two one-way trips of about 0.35 us between idle
+// workgroups, twice that under the polling of 200, are on every iteration's path): the first and the last
 // own knot's entries of each published vector to the neighbours, theirs into the
 // registers of the lane groups that multiply them, and two sums over the parts.
 // Vectors and sums count their exchanges separately (hx, sx).
@@ -1403,7 +1408,9 @@ struct PartExchange {
   int part, nparts, spin, tid, lane, slot, slot_r, p_r;   // last own knot: lane group slot_r, p_r-th of it
   bool has_l, has_r;                                      // a neighbour on the left / the right
   int *xfail;
+  double *total;                                          // LDS: the sums over the parts
   unsigned hx, sx;
+  static constexpr int kSumsWave = 2;
   __device__ __forceinline__ unsigned tag(unsigned e) const { return ((epoch & 0xffffu) << 16) | (e & 0xffffu); }
   __device__ __forceinline__ unsigned long long *at(int q, unsigned e) const {
     return xb + (size_t)q * kXPart + (size_t)(e % kXSlots) * kXSlot;
@@ -1426,20 +1433,31 @@ struct PartExchange {
     }
     ++hx;
   }
+  // One wavefront, next to neither neighbour, sends and collects the sums (with all
+  // eight polling the same words an iteration took 2.33 us instead of 1.95): sent as soon as this
+  // part's are known, collected into LDS before the barrier behind the next
+  // product, whose halo takes as long.
   __device__ __forceinline__ void put_sums(double a, double b) {
-    if (tid < 2) xput(at(part, sx) + 64 + 2 * tid, tag(sx), tid == 0 ? a : b);
+    if (tid >> 6 == kSumsWave && (tid & 63) < 2)
+      xput(at(part, sx) + 64 + 2 * (tid & 1), tag(sx), tid & 1 ? b : a);
   }
-  __device__ __forceinline__ void get_sums(double &a, double &b) {
-    const int l = tid & 63;
-    double v = 0.0;
-    if (l < 2 * nparts && !xget(at(l >> 1, sx) + 64 + 2 * (l & 1), tag(sx), *xfail != 0, spin, v)) *xfail = 1;
-    ++sx;
-    a = lane_val(v, 0) + lane_val(v, 2);
-    b = lane_val(v, 1) + lane_val(v, 3);
-    if (nparts == 4) {
-      a += lane_val(v, 4) + lane_val(v, 6);
-      b += lane_val(v, 5) + lane_val(v, 7);
+  __device__ __forceinline__ void wait_sums() {
+    if (tid >> 6 == kSumsWave) {
+      const int l = tid & 63;
+      double v = 0.0;
+      if (l < 2 * nparts && !xget(at(l >> 1, sx) + 64 + 2 * (l & 1), tag(sx), *xfail != 0, spin, v)) *xfail = 1;
+      double a = lane_val(v, 0) + lane_val(v, 2), b = lane_val(v, 1) + lane_val(v, 3);
+      if (nparts == 4) {
+        a += lane_val(v, 4) + lane_val(v, 6);
+        b += lane_val(v, 5) + lane_val(v, 7);
+      }
+      if (l < 2) total[l] = l ? b : a;
     }
+    ++sx;
+  }
+  __device__ __forceinline__ void get_sums(double &a, double &b) const {
+    a = total[0];
+    b = total[1];
   }
 };
 
@@ -1524,7 +1542,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
   for (int t = tid; t < PcgBufs<ND, K>::KH * G; t += kBlock) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
   if (tid < 64) sm.pcg.red[tid] = 0.0;
   PartExchange<ND, K> xch{a.xch + D.xch_off, a.epoch, part, nparts, a.xspin > 0 ? a.xspin : kXSpin, tid, lane0, slot0,
-                          (nloc - 1) % SLOTS, nloc > SLOTS ? 1 : 0, has_l, has_r, &sm.xfail, 0u, 0u};
+                          (nloc - 1) % SLOTS, nloc > SLOTS ? 1 : 0, has_l, has_r, &sm.xfail, sm.total, 0u, 0u};
   __syncthreads();
 
   for (int it = 0; it < a.iters; ++it) {
