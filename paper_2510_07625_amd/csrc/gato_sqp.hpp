@@ -283,6 +283,35 @@ __device__ __forceinline__ void row_dot1(double &acc, double x, const double *c)
   }
 }
 
+// acc += sum over the velocity entries m = NX/2..NX-1 only, of coefficients
+// c[m - NX/2].
+#define GATO_NBV(M, C) "v_fmac_f64_dpp %0, %1, %[c" #C "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t"
+#define GATO_NBV8(C, M, H)                                                             \
+  "v_fmac_f64_dpp %0, %2, %[c" #C "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_fmac_f64_dpp %1, %2, %[c" #C "] row_newbcast:" #H " row_mask:0xf bank_mask:0xf\n\t"
+template <int NX>
+__device__ __forceinline__ void row_dot1_vel(double &acc, double x, const double *c) {
+  static_assert(NX == 6 || NX == 12 || NX == 14, "8-lane groups hold 6 rows, 16-lane groups 12 or 14");
+  if constexpr (NX == 6) {
+    double hi = acc;
+    asm volatile("s_nop 1\n\t" GATO_NBV8(0, 3, 11) GATO_NBV8(1, 4, 12) GATO_NBV8(2, 5, 13)
+                 : "+v"(acc), "+v"(hi) : "v"(x), [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]));
+    acc = (threadIdx.x & 8) ? hi : acc;
+  } else if constexpr (NX == 14) {
+    asm volatile("s_nop 1\n\t" GATO_NBV(7, 0) GATO_NBV(8, 1) GATO_NBV(9, 2) GATO_NBV(10, 3) GATO_NBV(11, 4)
+                 GATO_NBV(12, 5) GATO_NBV(13, 6)
+                 : "+v"(acc) : "v"(x), [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]), [c3] "v"(c[3]),
+                   [c4] "v"(c[4]), [c5] "v"(c[5]), [c6] "v"(c[6]));
+  } else {
+    asm volatile("s_nop 1\n\t" GATO_NBV(6, 0) GATO_NBV(7, 1) GATO_NBV(8, 2) GATO_NBV(9, 3) GATO_NBV(10, 4)
+                 GATO_NBV(11, 5)
+                 : "+v"(acc) : "v"(x), [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]), [c3] "v"(c[3]),
+                   [c4] "v"(c[4]), [c5] "v"(c[5]));
+  }
+}
+#undef GATO_NBV
+#undef GATO_NBV8
+
 // acc -= sum_m c[m] x_m, m = 0..NX-1 in order (the same roundings as
 // acc = fma(-c[m], x_m, acc) term by term).
 #define GATO_NBN(M, C) "v_fmac_f64_dpp %0, -%1, %[c" #M "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t"
@@ -591,20 +620,52 @@ struct BlockSums {
 
 // The off-diagonal product at one knot of a lane group: y +- (O x)_k at this
 // lane's row, xl and xr being its entries of x_{k-1} and x_{k+1}.
+// (xs: x_{k+1} at this lane's row for joint rows, at the row of the same joint's
+// angle for velocity rows.)
 // From rows in registers:
 template <int ND, int K>
 struct OffRows {
+  static constexpr bool shifted = false;
   const double (&Am)[K][2 * ND];
   const double (&Ac)[K][2 * ND];
-  __device__ __forceinline__ void add(int p, double &y, double xl, double xr) const {
+  __device__ __forceinline__ void add(int p, double &y, double xl, double xr, double) const {
     row_dot1<2 * ND>(y, xl, Am[p]);
     row_dot1<2 * ND>(y, xr, Ac[p]);
   }
-  __device__ __forceinline__ void sub(int p, double &y, double xl, double xr) const {
+  __device__ __forceinline__ void sub(int p, double &y, double xl, double xr, double) const {
     row_dot1_sub<2 * ND>(y, xl, Am[p]);
     row_dot1_sub<2 * ND>(y, xr, Ac[p]);
   }
-  __device__ __forceinline__ void add_col(int p, double &y, double xr) const { row_dot1<2 * ND>(y, xr, Ac[p]); }
+  __device__ __forceinline__ void add_col(int p, double &y, double xr, double) const {
+    row_dot1<2 * ND>(y, xr, Ac[p]);
+  }
+};
+// With the joint rows of A_k known to be [I, hI] (the Euler step's), their part
+// of the column of A_k is one entry: Av, the velocity rows' part, and aj, the
+// coefficient of xs. 128 -> 117 vector instructions per iteration at one knot per
+// lane group and 234 -> 212 at two, the loops' bound (7 DoF, 256 solves of two SQP
+// iterations: N = 32 332 -> 322 us; closed-loop tick at N = 64 1690 -> 1616 us).
+// Blocks given by the caller and tip tracking's rewritten A_k have no such rows and
+// keep OffRows.
+template <int ND, int K>
+struct OffEuler {
+  static constexpr bool shifted = true;
+  const double (&Am)[K][2 * ND];
+  const double (&Av)[K][ND];
+  const double (&aj)[K];
+  __device__ __forceinline__ void add(int p, double &y, double xl, double xr, double xs) const {
+    row_dot1<2 * ND>(y, xl, Am[p]);
+    add_col(p, y, xr, xs);
+  }
+  __device__ __forceinline__ void sub(int p, double &y, double xl, double xr, double xs) const {
+    double t = 0.0;
+    add(p, t, xl, xr, xs);
+    y -= t;
+  }
+  __device__ __forceinline__ void add_col(int p, double &y, double xr, double xs) const {
+    y += aj[p] * xs;
+    row_dot1_vel<2 * ND>(y, xr, Av[p]);
+  }
 };
 // From the velocity rows of A in LDS (four knots per lane group): the row of
 // A_{k-1} is read as 2 ND floats, the column of A_k as ND, and the joint rows'
@@ -667,7 +728,7 @@ struct OffLds {
     const double t = row(p, xl) + col(p, xr);
     y += valid(p) ? t : 0.0;
   }
-  __device__ __forceinline__ void add_col(int p, double &y, double xr) const {
+  __device__ __forceinline__ void add_col(int p, double &y, double xr, double) const {
     const double t = col(p, xr);
     y -= valid(p) ? t : 0.0;
   }
@@ -826,23 +887,31 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
       row_dot1<NX>(y[p], x[p], Pd[p]);
     });
   };
-  double xl[K], xr[K];   // the neighbours' entries of a published vector
+  double xl[K], xr[K], xs[K];   // the neighbours' entries of a published vector
+  const int lane_s = lane < ND ? lane : lane - ND;
   auto read = [&](const double (*buf)[G]) {
     each([&](int p) {
       xl[p] = buf[slot + p * SLOTS][lane];
       xr[p] = buf[slot + p * SLOTS + 2][lane];
+      xs[p] = Off::shifted && !X::on ? buf[slot + p * SLOTS + 2][lane_s] : 0.0;
     });
     xch.get(xl, xr);
+    if constexpr (Off::shifted && X::on) {
+      each([&](int p) {
+        const double angle = dpp<0x110 + ND>(xr[p]);   // the entry of lane - ND
+        xs[p] = lane < ND ? xr[p] : angle;
+      });
+    }
   };
   auto off = [&](double *y) {   // y = O x
     each([&](int p) {
       y[p] = 0.0;
-      o.add(p, y[p], xl[p], xr[p]);
+      o.add(p, y[p], xl[p], xr[p], xs[p]);
     });
   };
   auto off_sub = [&](double *y) {   // y -= O x
     each([&](int p) {
-      o.sub(p, y[p], xl[p], xr[p]);
+      o.sub(p, y[p], xl[p], xr[p], xs[p]);
     });
   };
   double u[K], w[K], z[K], y[K], v[K];
@@ -1348,6 +1417,7 @@ struct PartSmem {
   float Lf[KH][NL];
   PcgBufs<ND, K> pcg;      // rows by local index
   double total[2];         // sums over the parts
+  double lam[KS][G];       // multipliers between the PCGs
   double piv[Sh::SLOTS][G];
   double mp0[KH];
   double Qi[G], Qni[G];
@@ -1536,6 +1606,16 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     const int i = slot0 + p * SLOTS;
     lam[p] = (a.warm && i < nloc && lane0 < NX) ? gL[min(kf + i + sh, N - 1) * a.nx_max + lane0] : 0.0;
   }
+  // (In LDS outside the PCG, as in sqp_solve.)
+  auto park = [&]() {
+#pragma unroll
+    for (int p = 0; p < K; ++p) sm.lam[slot0 + p * SLOTS][lane0] = lam[p];
+  };
+  auto unpark = [&]() {
+#pragma unroll
+    for (int p = 0; p < K; ++p) lam[p] = sm.lam[slot0 + p * SLOTS][lane0];
+  };
+  park();
   double rho = a.rho[sid];
   // (Rows without a knot and the partial sums of wavefronts without knots are
   // never written in the PCG.)
@@ -1551,6 +1631,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     if (!a.warm && it > 0) {
 #pragma unroll
       for (int p = 0; p < K; ++p) lam[p] = 0.0;
+      park();
     }
     if (tid < G) {
       // (Task-space form: the joint block of the rewritten Q_k is the identity.)
@@ -1679,6 +1760,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     }
     __syncthreads();
     if (tid == 0) sm.bad[(it + 1) & 1] = 0;
+    unpark();
     if constexpr (TS) {
       // Tip costs of the own knots into the merit terms; the QP data of the
       // own knots and the left halo rewritten in y_k = T_k^-1 x_k; then the
@@ -1699,14 +1781,24 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     if (clk) clk[1] = wall_clock64();
 
     // ================= 2. Schur rows and diagonal-block inverses of the own knots.
-    double Am[K][NX], Ac[K][NX], Pd[K][NX], gam[K], res[K], qown[K];
+    // (The whole column of A_k for tip tracking and where the exchange, not the FMAs,
+    // sets the pace: 1.95 against 2.01 us per iteration with one knot per lane group;
+    // OffEuler's with two, 2.27 against 2.35.)
+    constexpr bool kRows = TS || K == 1;
+    double Am[K][NX], Ac[kRows ? K : 1][NX], Av[K][ND], aj[K], Pd[K][NX], gam[K], res[K], qown[K];
 #pragma unroll
     for (int p = 0; p < K; ++p) {
       const int i = slot + p * SLOTS, li = i + 1, k = kf + i;
       double thr[NX];
       gam[p] = res[p] = qown[p] = 0.0;
 #pragma unroll
-      for (int m = 0; m < NX; ++m) thr[m] = Am[p][m] = Ac[p][m] = Pd[p][m] = 0.0;
+      for (int m = 0; m < NX; ++m) {
+        thr[m] = Am[p][m] = Pd[p][m] = 0.0;
+        if constexpr (kRows) Ac[p][m] = 0.0;
+      }
+      aj[p] = 0.0;
+#pragma unroll
+      for (int m = 0; m < ND; ++m) Av[p][m] = 0.0;
       if (i < nloc) {
         const double *Qik = (k < N - 1) ? sm.Qi : sm.Qni;
         if (lane < NX) {
@@ -1718,8 +1810,14 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
                          sm.qg[li - 1], sm.rg[li - 1], lam[p], thr, gam[p], res[p]);
           if (k < N - 1) {
             const float *An = sm.A[li];
+            if constexpr (kRows) {
 #pragma unroll
-            for (int m = 0; m < NX; ++m) Ac[p][m] = -qown[p] * (double)An[m * NX + lane];
+              for (int m = 0; m < NX; ++m) Ac[p][m] = -qown[p] * (double)An[m * NX + lane];
+            } else {
+              aj[p] = -qown[p] * (lane < ND ? 1.0 : (double)h);
+#pragma unroll
+              for (int m = 0; m < ND; ++m) Av[p][m] = -qown[p] * (double)An[(ND + m) * NX + lane];
+            }
           }
         }
         invert_knot<ND, !TS>(lane, k == 0, sm.Qi, thr, sm.piv[slot], Pd[p]);
@@ -1732,7 +1830,10 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     // ================= 3-4. Preconditioned CG, entries and sums through the exchange.
     const int max_it = a.pcg_max_iter > 0 ? a.pcg_max_iter : N * NX;
     const int slot_w = (__builtin_amdgcn_readfirstlane(tid) >> 6) * (64 / G);   // the wavefront's first lane group
-    const OffRows<ND, K> off{Am, Ac};
+    auto off = [&]() {
+      if constexpr (kRows) return OffRows<ND, K>{Am, Ac};
+      else return OffEuler<ND, K>{Am, Av, aj};
+    }();
     bool capped = false;
     int its;
     if (K > 1 && slot_w + SLOTS < nloc)
@@ -1817,6 +1918,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
       }
       if (has_l && slot == 0) to_x(0);
     }
+    park();
     __syncthreads();
     {
       // The first own knot's step to the left: a part reads its right neighbour's
@@ -1974,6 +2076,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     if (j < NX) a.X[xoff + (size_t)kk * a.nx_max + j] = sm.X[lg][j];
     if (kk < N - 1 && j < NU) a.U[uoff + (size_t)kk * a.nu_max + j] = sm.U[lg][j];
   }
+  unpark();
 #pragma unroll
   for (int p = 0; p < K; ++p) {
     const int i = slot0 + p * SLOTS;
@@ -2319,11 +2422,14 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     bool xfail_any = false;   // some part of this solve gave up a wait
     if constexpr (kHalf) {
       // ================= 2. Schur rows and diagonal-block inverses, lane = row.
-      double Am[kLong ? 1 : KPT][NX], Ac[kLong ? 1 : KPT][NX];   // rows of O_{k,k-1} and O_{k,k+1} (OffRows)
+      // Rows of O_{k,k-1} and O_{k,k+1} (OffEuler; OffRows where the joint rows of A
+      // are not the Euler step's: tip tracking, caller-given QP data).
+      constexpr int KA = kLong ? 1 : KPT;
+      double Am[KA][NX], Av[KA][ND], aj[KA];
       double Pd[KPT][NX];                                        // row of D_k^-1
       double gam[KPT], res[KPT], qown[KPT];
-      // The A blocks of the long form as they are (caller-given QP data only).
-      const float *full = kLong && a.mode == kModeKkt ? Ablk(0) : nullptr;
+      // The A blocks as they are.
+      const float *full = TS || a.mode == kModeKkt ? Ablk(0) : nullptr;
       if constexpr (kLong) {
         for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += kBlock) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
         if (tid < 64) sm.pcg.red[tid] = 0.0;
@@ -2336,7 +2442,12 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 #pragma unroll
         for (int m = 0; m < NX; ++m) {
           thr[m] = Pd[p][m] = 0.0;
-          if constexpr (!kLong) Am[p][m] = Ac[p][m] = 0.0;
+          if constexpr (!kLong) Am[p][m] = 0.0;
+        }
+        if constexpr (!kLong) {
+          aj[p] = 0.0;
+#pragma unroll
+          for (int m = 0; m < ND; ++m) Av[p][m] = 0.0;
         }
         if (k < N) {
           const double *Qik = (k < N - 1) ? sm.Qi : sm.Qni;
@@ -2356,11 +2467,12 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
             };
             schur_knot<ND>(lane, k == 0, arow, put, Ablk(km), Bblk(km), sm.Qi, Qik, D.Ri, sm.c0, sm.e[km], sm.qg[k],
                            sm.qg[km], sm.rg[km], lam[p], thr, gam[p], res[p]);
-            if constexpr (!kLong) {
+            if constexpr (!kLong && !TS) {
               if (k < N - 1) {
                 const float *A = Ablk(k);
+                aj[p] = -qown[p] * (lane < ND ? 1.0 : (double)h);
 #pragma unroll
-                for (int m = 0; m < NX; ++m) Ac[p][m] = -qown[p] * (double)A[m * NX + lane];
+                for (int m = 0; m < ND; ++m) Av[p][m] = -qown[p] * (double)A[(ND + m) * NX + lane];
               }
             }
           }
@@ -2377,27 +2489,37 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       const int max_it = a.pcg_max_iter > 0 ? a.pcg_max_iter : N * NX;
       const int slot_w = (__builtin_amdgcn_readfirstlane(tid) >> 6) * (64 / G);   // the wavefront's first lane group
       NoExchange none;
-      auto off = [&]() {
-        if constexpr (kLong)
-          return OffLds<ND, KPT, false>{sm.Av, nullptr, qown, lane < NX ? sm.Qi[lane] : 0.0, (double)h, lane, slot, N};
-        else
-          return OffRows<ND, KPT>{Am, Ac};
-      }();
-      const OffLds<ND, KPT, true> off_full{nullptr, full, qown, lane < NX ? sm.Qi[lane] : 0.0, 0.0, lane, slot, N};
+      auto pcg = [&](auto na, auto pipe, const auto &off) {
+        its = pcg_half_sweeps<ND, KPT, na, pipe>(sm.pcg, tid, lane, slot, off, none, Pd, gam, res, lam, a.pcg_tol,
+                                                 max_it, capped);
+      };
+      using std::integral_constant;
+      const double q0 = lane < NX ? sm.Qi[lane] : 0.0;
+      const OffLds<ND, KPT, true> off_full{nullptr, full, qown, q0, 0.0, lane, slot, N};
       if constexpr (kLong) {
         int na = 0;
         for (int p = 0; p < KPT; ++p) na += slot_w + p * SLOTS < N ? 1 : 0;
+        const OffLds<ND, KPT, false> off{sm.Av, nullptr, qown, q0, (double)h, lane, slot, N};
         its = full ? pcg_long<ND, KPT>(sm.pcg, tid, lane, slot, na, off_full, Pd, gam, res, lam, a.pcg_tol, max_it, capped)
                    : pcg_long<ND, KPT>(sm.pcg, tid, lane, slot, na, off, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
-      } else if (KPT > 1 && slot_w + SLOTS < N) {
-        its = pcg_half_sweeps<ND, KPT, KPT, !TS>(sm.pcg, tid, lane, slot, off, none, Pd, gam, res, lam, a.pcg_tol,
-                                                 max_it, capped);
-      } else if (slot_w < N) {
-        its = pcg_half_sweeps<ND, KPT, 1, !TS>(sm.pcg, tid, lane, slot, off, none, Pd, gam, res, lam, a.pcg_tol,
-                                               max_it, capped);
-      } else {
-        its = pcg_half_sweeps<ND, KPT, 0, !TS>(sm.pcg, tid, lane, slot, off, none, Pd, gam, res, lam, a.pcg_tol,
-                                               max_it, capped);
+      } else if (TS || full) {
+        double Ac[KPT][NX];
+#pragma unroll
+        for (int p = 0; p < KPT; ++p) {
+          const int k = slot + p * SLOTS;
+          const float *A = full + (size_t)min(k, N - 2) * NX * NX;
+#pragma unroll
+          for (int m = 0; m < NX; ++m) Ac[p][m] = k < N - 1 && lane < NX ? -qown[p] * (double)A[m * NX + lane] : 0.0;
+        }
+        const OffRows<ND, KPT> off{Am, Ac};
+        if (KPT > 1 && slot_w + SLOTS < N) pcg(integral_constant<int, KPT>{}, integral_constant<bool, !TS>{}, off);
+        else if (slot_w < N) pcg(integral_constant<int, 1>{}, integral_constant<bool, !TS>{}, off);
+        else pcg(integral_constant<int, 0>{}, integral_constant<bool, !TS>{}, off);
+      } else if constexpr (!TS) {
+        const OffEuler<ND, KPT> off{Am, Av, aj};
+        if (KPT > 1 && slot_w + SLOTS < N) pcg(integral_constant<int, KPT>{}, std::true_type{}, off);
+        else if (slot_w < N) pcg(integral_constant<int, 1>{}, std::true_type{}, off);
+        else pcg(integral_constant<int, 0>{}, std::true_type{}, off);
       }
       if (clk) clk[4] = wall_clock64();
       // (z: last read before the last barrier of the PCG's loop.)
@@ -2409,8 +2531,22 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
         const int k = slot + p * SLOTS;
         if (k < N && lane < NX) {
           double d = -qown[p] * ((double)sm.qg[k][lane] - lam[p]);
-          if (kLong && full) off_full.add_col(p, d, sm.pcg.z[k + 2][lane]);
-          else off.add_col(p, d, sm.pcg.z[k + 2][lane]);
+          const double *ln = sm.pcg.z[k + 2];
+          if constexpr (kLong) {
+            const OffLds<ND, KPT, false> off{sm.Av, nullptr, qown, q0, (double)h, lane, slot, N};
+            if (full) off_full.add_col(p, d, ln[lane], 0.0);
+            else off.add_col(p, d, ln[lane], 0.0);
+          } else if (TS || full) {
+            if (k < N - 1) {
+              const float *A = Ablk(k);
+              double t = 0.0;
+#pragma unroll
+              for (int m = 0; m < NX; ++m) t += (double)A[m * NX + lane] * ln[m];
+              d -= qown[p] * t;
+            }
+          } else {
+            OffEuler<ND, KPT>{Am, Av, aj}.add_col(p, d, ln[lane], ln[lane < ND ? lane : lane - ND]);
+          }
           const float dx = (float)d;
           sm.dX[k][lane] = dx;
           if (!isfinite(dx)) bad_flag = 1;
