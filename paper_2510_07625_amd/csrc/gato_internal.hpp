@@ -8,7 +8,7 @@
 
 namespace gato {
 
-constexpr int kBlock = 512;        // threads per workgroup (one solve per workgroup)
+constexpr int kBlock = 512;        // threads per workgroup (one solve per workgroup), at most
 constexpr int kMaxAlpha = GATO_MAX_ALPHA;
 
 // Per-solve constants, built on the host at create time.

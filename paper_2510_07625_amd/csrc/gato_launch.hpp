@@ -94,4 +94,18 @@ inline int kpt_for(int n, int N) {
   return 0;
 }
 
+// Threads of a one-shape launch. Knots that do not exist leave their lane groups
+// idle, so at one knot per lane group the workgroup holds the wavefronts that the
+// batch's longest horizon and its line search (a thread per candidate and knot)
+// need. Up to 256 threads, two workgroups share a CU (256 VGPRs, at most 79 KB of
+// LDS), so that more solves than CUs run together: N = 16 or less in 6-7 DoF.
+// One SQP iteration, 6 DoF, N = 8, against 512 threads: 512 solves 92 -> 60 us, one
+// solve 47.5 -> 45.4 (barriers of two wavefronts instead of eight).
+inline int block_threads(int n, int kpt, const KArgs &a) {
+  if (kpt != 1) return kBlock;
+  const int G = (2 * n > 8) ? 16 : 8;
+  const int need = a.N_max * G > a.n_alpha * (a.N_max - 1) ? a.N_max * G : a.n_alpha * (a.N_max - 1);
+  return need >= kBlock ? kBlock : (need + 63) / 64 * 64;
+}
+
 }  // namespace gato

@@ -1,6 +1,6 @@
 // The fused SQP iteration for one trajectory-optimisation solve per workgroup.
 //
-// One workgroup of kBlock threads owns one solve and runs whole SQP iterations
+// One workgroup of up to kBlock threads owns one solve and runs whole SQP iterations
 // (Algorithm 1) without returning to the host. Knot k of the solve is handled
 // by a group of G lanes (G = 16 for 5..7 DoF, 8 for fewer), so a wavefront
 // holds 64/G knots. Per iteration:
@@ -2155,15 +2155,18 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
   constexpr bool kThGlobal = KPT >= 4;
   auto Tblk = [&](int k) -> Real * { return reinterpret_cast<Real *>(ws + D.offT) + (size_t)k * NX * NX; };
 
+  // (One knot per lane group: the launch's own workgroup size, block_threads().)
+  const int nthr = KPT == 1 ? (int)blockDim.x : kBlock;
+
   // ---- Stage the iterate and the solve constants in LDS.
   // (With a warm-start shift, knot k starts from the previous knot k + shift,
   // the last knot repeated.)
-  for (int t = tid; t < N * G; t += kBlock) {
+  for (int t = tid; t < N * G; t += nthr) {
     const int k = t / G, j = t % G;
     const int ks = min(k + sh, N - 1);
     sm.X[k][j] = (j < NX && a.mode != kModeKkt) ? a.X[xoff + (size_t)ks * a.nx_max + j] : 0.f;
   }
-  for (int t = tid; t < (N - 1) * 8; t += kBlock) {
+  for (int t = tid; t < (N - 1) * 8; t += nthr) {
     const int k = t / 8, j = t % 8;
     const int ks = min(k + sh, N - 2);
     sm.U[k][j] = (j < NU && a.mode != kModeKkt) ? a.U[uoff + (size_t)ks * a.nu_max + j] : 0.f;
@@ -2175,7 +2178,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
   }
   if constexpr (TS) {
     // Reference tip positions of this request's horizon (not shifted).
-    for (int t = tid; t < N * 4; t += kBlock) {
+    for (int t = tid; t < N * 4; t += nthr) {
       const int k = t / 4, c = t % 4;
       ts.pr[k][c] = c < 3 ? a.pref[((size_t)sid * a.N_max + k) * 3 + c] : 0.f;
     }
@@ -2193,9 +2196,12 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 
   if constexpr (kHalf && !kLong) {
     // (Knots beyond the horizon and the partial sums of wavefronts without
-    // knots are never written in the PCG.)
-    for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += kBlock) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
+    // knots, or of those a smaller workgroup has not, are never written in the PCG.)
+    for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += nthr) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
     if (tid < 64) sm.pcg.red[tid] = 0.0;
+  }
+  if constexpr (!kHalf && KPT == 1) {
+    if (tid < 2 * 3 * (kBlock / 64)) (&sm.red[0][0][0])[tid] = 0.0;
   }
   // Multipliers of the rows this thread owns (warm start across iterations).
   Real lam[KPT];
@@ -2331,14 +2337,14 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
           }
         }
       }
-      for (int t = tid; t < N * G; t += kBlock) {
+      for (int t = tid; t < N * G; t += nthr) {
         const int k = t / G, j = t % G;
         const float *W = (k < N - 1) ? D.Wq : D.Wn;
         sm.qg[k][j] = j < NX ? W[j] * (sm.X[k][j] - sm.xg[j]) : 0.f;
         if (k < N - 1 && j < 8) sm.rg[k][j] = j < NU ? D.Wr[j] * sm.U[k][j] : 0.f;
       }
       if (tid < G) sm.c0[tid] = tid < NX ? sm.xs[tid] - sm.X[0][tid] : 0.f;
-      if (tid == kBlock - 1) {
+      if (tid == nthr - 1) {
         float cost = 0.f, viol = 0.f;
         for (int i = 0; i < NX; ++i) {
           const float d = sm.X[N - 1][i] - sm.xg[i];
@@ -2358,15 +2364,15 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
         const size_t ao = (size_t)sid * (a.N_max - 1) * a.nx_max * a.nx_max;
         const size_t bo = (size_t)sid * (a.N_max - 1) * a.nx_max * a.nu_max;
         const size_t eo = (size_t)sid * (a.N_max - 1) * a.nx_max;
-        for (int t = tid; t < (N - 1) * NX * NX; t += kBlock) {
+        for (int t = tid; t < (N - 1) * NX * NX; t += nthr) {
           const int k = t / (NX * NX), r = (t / NX) % NX, c = t % NX;
           a.outA[ao + ((size_t)k * a.nx_max + r) * a.nx_max + c] = Ablk(k)[r * NX + c];
         }
-        for (int t = tid; t < (N - 1) * NX * NU; t += kBlock) {
+        for (int t = tid; t < (N - 1) * NX * NU; t += nthr) {
           const int k = t / (NX * NU), r = (t / NU) % NX, c = t % NU;
           a.outB[bo + ((size_t)k * a.nx_max + r) * a.nu_max + c] = Bblk(k)[r * NU + c];
         }
-        for (int t = tid; t < (N - 1) * NX; t += kBlock) {
+        for (int t = tid; t < (N - 1) * NX; t += nthr) {
           const int k = t / NX, r = t % NX;
           a.oute[eo + (size_t)k * a.nx_max + r] = sm.e[k][r];
         }
@@ -2376,15 +2382,15 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       // Stage entry point: QP data supplied by the caller.
       const size_t ao = (size_t)sid * (a.N_max - 1) * a.nx_max * a.nx_max;
       const size_t bo = (size_t)sid * (a.N_max - 1) * a.nx_max * a.nu_max;
-      for (int t = tid; t < (N - 1) * NX * NX; t += kBlock) {
+      for (int t = tid; t < (N - 1) * NX * NX; t += nthr) {
         const int k = t / (NX * NX), r = (t / NX) % NX, c = t % NX;
         Ablk(k)[r * NX + c] = a.inA[ao + ((size_t)k * a.nx_max + r) * a.nx_max + c];
       }
-      for (int t = tid; t < (N - 1) * NX * NU; t += kBlock) {
+      for (int t = tid; t < (N - 1) * NX * NU; t += nthr) {
         const int k = t / (NX * NU), r = (t / NU) % NX, c = t % NU;
         Bblk(k)[r * NU + c] = a.inB[bo + ((size_t)k * a.nx_max + r) * a.nu_max + c];
       }
-      for (int t = tid; t < N * G; t += kBlock) {
+      for (int t = tid; t < N * G; t += nthr) {
         const int k = t / G, j = t % G;
         sm.qg[k][j] = j < NX ? a.inq[xoff + (size_t)k * a.nx_max + j] : 0.f;
         if (k < N - 1) {
@@ -2400,7 +2406,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     if (tid == 0) sm.bad[(it + 1) & 1] = 0;
     unpark();
     if constexpr (TS) {
-      for (int t = tid; t < N; t += kBlock) sm.mp0[t] += ts.mt[t];
+      for (int t = tid; t < N; t += nthr) sm.mp0[t] += ts.mt[t];
       // Rewrite the QP in y_k = T_k^-1 x_k, and the warm-start multipliers
       // (lambda^ = T_k^T lambda).
 #pragma unroll
@@ -2431,7 +2437,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       // The A blocks as they are.
       const float *full = TS || a.mode == kModeKkt ? Ablk(0) : nullptr;
       if constexpr (kLong) {
-        for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += kBlock) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
+        for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += nthr) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
         if (tid < 64) sm.pcg.red[tid] = 0.0;
       }
 #pragma unroll
@@ -3204,7 +3210,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
 
     // ================= 6. Line search over alpha_i = beta^-i (Eqs. (3), (7)).
     const int ntask = n_alpha * (N - 1);
-    for (int t = tid; t < ntask; t += kBlock) {
+    for (int t = tid; t < ntask; t += nthr) {
       const int i = t / (N - 1), k = t - i * (N - 1);
       const float al = sm.alpha[i];
       float q[ND], qd[ND], uu[ND], qdd[ND], L[ND][ND], xn[NX];
@@ -3235,7 +3241,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       }
       sm.mp[i][k] = (double)cost + (double)a.mu * (double)viol;
     }
-    for (int i = tid; i < n_alpha; i += kBlock) {
+    for (int i = tid; i < n_alpha; i += nthr) {
       const float al = sm.alpha[i];
       float cost = 0.f, viol = 0.f;
       for (int j = 0; j < NX; ++j) {
@@ -3275,7 +3281,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     if (a.rho_adapt) rho = (status & (GATO_ST_NONFINITE | GATO_ST_NO_DESCENT)) ? fmin(2.0 * rho, 1e8) : rho / 3.0;
     const float al = bad ? 0.f : sm.alpha[best];
     if (!bad) {
-      for (int t = tid; t < N * G; t += kBlock) {
+      for (int t = tid; t < N * G; t += nthr) {
         const int k = t / G, j = t % G;
         sm.X[k][j] += al * sm.dX[k][j];
         if (k < N - 1 && j < 8) sm.U[k][j] += al * sm.dU[k][j];
@@ -3306,7 +3312,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     if (a.rho_adapt && tid == 0) a.rho[sid] = rho;
     const size_t rxo = (size_t)blockIdx.x * a.N_max * a.nx_max;
     const size_t ruo = (size_t)blockIdx.x * (a.N_max - 1) * a.nu_max;
-    for (int t = tid; t < N * G; t += kBlock) {
+    for (int t = tid; t < N * G; t += nthr) {
       const int k = t / G, j = t % G;
       if (j < NX) {
         a.X[xoff + (size_t)k * a.nx_max + j] = sm.X[k][j];

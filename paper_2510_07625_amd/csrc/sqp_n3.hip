@@ -5,7 +5,7 @@
 namespace gato {
 
 hipError_t launch_sqp_n3(int kpt, bool f64, int grid, const KArgs &a, hipStream_t s) {
-  const dim3 g(grid), b(kBlock);
+  const dim3 g(grid), b(block_threads(3, kpt, a));
   switch (kpt * 2 + (f64 ? 1 : 0)) {
     case 2: hipLaunchKernelGGL((sqp_kernel<3, 1, float>), g, b, 0, s, a); break;
     case 3: hipLaunchKernelGGL((sqp_kernel<3, 1, double>), g, b, 0, s, a); break;

@@ -6,7 +6,7 @@
 namespace gato {
 
 hipError_t launch_sqp_task(int nd, int kpt, bool f64, int grid, const KArgs &a, hipStream_t s) {
-  const dim3 g(grid), b(kBlock);
+  const dim3 g(grid), b(block_threads(nd, kpt, a));
   switch (nd * 8 + kpt * 2 + (f64 ? 1 : 0)) {
     case 7 * 8 + 2: hipLaunchKernelGGL((sqp_kernel<7, 1, float, true>), g, b, 0, s, a); break;
     case 7 * 8 + 3: hipLaunchKernelGGL((sqp_kernel<7, 1, double, true>), g, b, 0, s, a); break;
