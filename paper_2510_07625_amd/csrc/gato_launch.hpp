@@ -105,7 +105,7 @@ inline int block_threads(int n, int kpt, const KArgs &a) {
   if (kpt != 1) return kBlock;
   const int G = (2 * n > 8) ? 16 : 8;
   const int need = a.N_max * G > a.n_alpha * (a.N_max - 1) ? a.N_max * G : a.n_alpha * (a.N_max - 1);
-  return need >= kBlock ? kBlock : (need + 63) / 64 * 64;
+  return need >= kBlock ? kBlock : need <= 128 ? 128 : (need + 63) / 64 * 64;   // (two halves of the dynamics)
 }
 
 }  // namespace gato

@@ -71,8 +71,7 @@ template <class S> struct cst_impl<dual<S>> {
 template <class T> __host__ __device__ inline T cst(float x) { return cst_impl<T>::make(x); }
 
 __host__ __device__ inline void sin_cos(float x, float *s, float *c) {
-  *s = sinf(x);
-  *c = cosf(x);
+  sincosf(x, s, c);   // (one range reduction for both)
 }
 __host__ __device__ inline void sin_cos(double x, double *s, double *c) {
   *s = sin(x);
@@ -242,19 +241,25 @@ __host__ __device__ inline void rnea(const Chain &ch, const T *q, const T *cq, c
 // and one link offset at a time. With T a dual number seeded on q_j it also
 // gives column j of the tip Jacobian.
 // ---------------------------------------------------------------------------
+// cq, sq: cos and sin of the joint angles.
 template <int ND, class T>
-__host__ __device__ inline void tip_position(const Chain &ch, const T *q, T *p) {
+__host__ __device__ inline void tip_position(const Chain &ch, const T *cq, const T *sq, T *p) {
   p[0] = cst<T>(0.f);
   p[1] = cst<T>(0.f);
   p[2] = cst<T>(ch.Lt);
 #pragma unroll
   for (int i = ND - 1; i >= 0; --i) {
-    T s, c;
-    sin_cos(q[i], &s, &c);
-    if (i & 1) rot_R<true>(c, s, p[0], p[1], p[2]);
-    else rot_R<false>(c, s, p[0], p[1], p[2]);
+    if (i & 1) rot_R<true>(cq[i], sq[i], p[0], p[1], p[2]);
+    else rot_R<false>(cq[i], sq[i], p[0], p[1], p[2]);
     if (i > 0) p[2] = p[2] + cst<T>(ch.Lp[i]);
   }
+}
+template <int ND, class T>
+__host__ __device__ inline void tip_position(const Chain &ch, const T *q, T *p) {
+  T c[ND], s[ND];
+#pragma unroll
+  for (int i = 0; i < ND; ++i) sin_cos(q[i], &s[i], &c[i]);
+  tip_position<ND, T>(ch, c, s, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -401,34 +406,47 @@ __host__ __device__ inline void chol_solve(const S (*L)[ND], S *b) {
   }
 }
 
-// Forward dynamics qdd = M(q)^-1 (tau - b(q, qd)). Leaves the Cholesky factor
-// of M in L for later solves. Returns false if M is not positive definite.
+// The two independent halves of forward dynamics qdd = M(q)^-1 (tau - b(q, qd)):
+// the Cholesky factor L of M (false if M is not positive definite) and the bias
+// forces b.
 template <int ND, class S>
-__host__ __device__ inline bool forward_dynamics(const Chain &ch, const S *q, const S *qd, const S *tau, S *qdd,
-                                                 S (*L)[ND]) {
-  S cq[ND], sq[ND];
-#pragma unroll
-  for (int i = 0; i < ND; ++i) sin_cos(q[i], &sq[i], &cq[i]);
+__host__ __device__ inline bool fd_inertia(const Chain &ch, const S *cq, const S *sq, S (*L)[ND]) {
   crba<ND, S>(ch, cq, sq, L);
-  S zero[ND], b[ND];
+  return cholesky<ND, S>(L);
+}
+template <int ND, class S>
+__host__ __device__ inline void fd_bias(const Chain &ch, const S *q, const S *cq, const S *sq, const S *qd, S *b) {
+  S zero[ND];
 #pragma unroll
   for (int i = 0; i < ND; ++i) zero[i] = S(0.f);
   rnea<ND, S>(ch, q, cq, sq, qd, zero, true, b);
-  const bool ok = cholesky<ND, S>(L);
+}
+template <int ND, class S>
+__host__ __device__ inline void fd_solve(const S (*L)[ND], const S *tau, const S *b, S *qdd) {
 #pragma unroll
   for (int i = 0; i < ND; ++i) qdd[i] = tau[i] - b[i];
   chol_solve<ND, S>(L, qdd);
+}
+
+// Forward dynamics. Leaves the Cholesky factor of M in L for later solves.
+// Returns false if M is not positive definite.
+template <int ND, class S>
+__host__ __device__ inline bool forward_dynamics(const Chain &ch, const S *q, const S *qd, const S *tau, S *qdd,
+                                                 S (*L)[ND]) {
+  S cq[ND], sq[ND], b[ND];
+#pragma unroll
+  for (int i = 0; i < ND; ++i) sin_cos(q[i], &sq[i], &cq[i]);
+  fd_bias<ND, S>(ch, q, cq, sq, qd, b);
+  const bool ok = fd_inertia<ND, S>(ch, cq, sq, L);
+  fd_solve<ND, S>(L, tau, b, qdd);
   return ok;
 }
 
 // -dID/dx_dir at fixed qdd, by one dual-number RNEA pass: direction dir < ND
-// is q_dir, dir >= ND is qd_(dir-ND).
+// is q_dir, dir >= ND is qd_(dir-ND). cv, sv: cos and sin of the joint angles.
 template <int ND, class S>
-__host__ __device__ inline void id_tangent(const Chain &ch, const S *q, const S *qd, const S *qdd, int dir,
-                                           S *col) {
-  S cv[ND], sv[ND];
-#pragma unroll
-  for (int i = 0; i < ND; ++i) sin_cos(q[i], &sv[i], &cv[i]);
+__host__ __device__ inline void id_tangent(const Chain &ch, const S *q, const S *cv, const S *sv, const S *qd,
+                                           const S *qdd, int dir, S *col) {
   // Only joint `dir` carries an angle tangent: d sin = cos, d cos = -sin.
   dual<S> Q[ND], CQ[ND], SQ[ND], QD[ND], QDD[ND], TAU[ND];
 #pragma unroll
@@ -443,6 +461,14 @@ __host__ __device__ inline void id_tangent(const Chain &ch, const S *q, const S 
   rnea<ND, dual<S>>(ch, Q, CQ, SQ, QD, QDD, true, TAU);
 #pragma unroll
   for (int i = 0; i < ND; ++i) col[i] = -TAU[i].d;
+}
+template <int ND, class S>
+__host__ __device__ inline void id_tangent(const Chain &ch, const S *q, const S *qd, const S *qdd, int dir,
+                                           S *col) {
+  S cv[ND], sv[ND];
+#pragma unroll
+  for (int i = 0; i < ND; ++i) sin_cos(q[i], &sv[i], &cv[i]);
+  id_tangent<ND, S>(ch, q, cv, sv, qd, qdd, dir, col);
 }
 
 // One column of the Jacobian of forward dynamics, dqdd/dx_dir = -M^-1 dID/dx_dir,

@@ -4,10 +4,11 @@
 // (Algorithm 1) without returning to the host. Knot k of the solve is handled
 // by a group of G lanes (G = 16 for 5..7 DoF, 8 for fewer), so a wavefront
 // holds 64/G knots. Per iteration:
-//   1. LQ (Sec. III-A, Eq. (1)): the group's first lane evaluates forward
-//      dynamics and the Cholesky factor of the inertia matrix and shares them
-//      through LDS; lane d then forms column d of the dynamics Jacobian with one
-//      dual-number RNEA pass. Defects, gradients and the current merit follow.
+//   1. LQ (Sec. III-A, Eq. (1)): a thread per knot and half evaluates forward
+//      dynamics (the inertia matrix's Cholesky factor; the bias forces) and shares
+//      it through LDS; lane d of the knot's group then forms column d of the
+//      dynamics Jacobian with one dual-number RNEA pass. Defects, gradients and the
+//      current merit follow.
 //   2. Schur complement (Eqs. (5)-(6)): lane j forms row j of theta_{k-1} and
 //      entry j of gamma~ in FP64, then the group inverts the diagonal block by
 //      Gauss-Jordan elimination (SPD, no pivoting).
@@ -27,8 +28,8 @@
 //      group take the sums behind a barrier of their own; the all-FP32 variant
 //      runs the standard arrangement.)
 //   5. Step dZ = -G^-1 (g - C^T lambda) (Eq. (4)).
-//   6. Line search (Eqs. (3), (7)): lane (alpha, knot) evaluates one trial
-//      knot; a fixed-order reduction gives each candidate's merit.
+//   6. Line search (Eqs. (3), (7)): thread (alpha, knot) evaluates one trial
+//      knot, or one thread each half of its dynamics; a fixed-order reduction gives each candidate's merit.
 // The Schur rows, gamma~, the block inverses, the PCG vectors and its inner
 // products use Real (double; float for the all-FP32 variant). Dynamics and the
 // line search's trial points use float; the explicit preconditioner blocks of
@@ -1216,21 +1217,257 @@ __device__ __forceinline__ bool xget(unsigned long long *w, unsigned tag, bool d
   return xget2(w, nullptr, tag, dead, spin, v, unused);
 }
 
+// A copy of uniform, constant data through scalar loads. The phases that run the
+// chain's dynamics take their own copy, through a solve index that the compiler
+// takes as new there: the constants stay in SGPRs, where references to the
+// descriptor kept them in vector registers across the SQP iterations (in scratch
+// for the most part) and loaded them per lane. (One knot per lane group, 7 DoF: 56
+// bytes of scratch before, none now.) Each part of a phase takes its own copy: held
+// over a whole phase they push the PCG's masks out of the SGPRs.
+template <class T>
+__device__ __forceinline__ T load_uniform(const T *p) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  typedef const unsigned __attribute__((address_space(4))) *Words;
+  const Words w = (Words)(p);
+  unsigned v[sizeof(T) / 4];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 4; ++i) v[i] = w[i];
+  T t;
+  __builtin_memcpy(&t, v, sizeof(T));
+  return t;
+}
+__device__ __forceinline__ const SolveDesc *fresh_desc(const KArgs &a, int sid) {
+  int s = __builtin_amdgcn_readfirstlane(sid);
+  asm volatile("" : "+s"(s));
+  return a.desc + s;
+}
+struct CostWeights {
+  float Wq[16], Wn[16], Wr[8];   // (as in SolveDesc)
+};
+static_assert(offsetof(SolveDesc, Wn) - offsetof(SolveDesc, Wq) == offsetof(CostWeights, Wn) &&
+                  offsetof(SolveDesc, Wr) - offsetof(SolveDesc, Wq) == offsetof(CostWeights, Wr),
+              "the descriptor's weights are copied as one block");
+__device__ __forceinline__ CostWeights load_weights(const SolveDesc *d) {
+  return load_uniform(reinterpret_cast<const CostWeights *>(d->Wq));
+}
+
+// ---- Phase 1 at the knots of the LDS rows row0 .. row0 + nq - 1: defects, merit
+// terms (rows from mp_from), A_k's and B_k's columns (stored by put_a, put_b; lane =
+// column), and the cos and sin of ntrig rows' joint angles in the rows of dX, which is
+// free until the step recovery.
+// The time is the chain of one knot's recursions, a wavefront's instructions one
+// after the other. So the sines and cosines are formed by a thread per angle, the
+// forward dynamics by a thread per knot instead of by one lane per lane group (one or
+// two wavefronts for all knots; up to four passes of the lane groups before), its two
+// independent halves, inertia and bias, in different wavefronts. 7 DoF N = 32 12.4 ->
+// 8.9 us, N = 64 24 -> 18, 32 knots of a split solve's part 11.7 -> 8.8; 6 DoF N = 128
+// 44 -> 26, N = 8 10 -> 7.
+template <int ND, class SM, class PutA, class PutB>
+__device__ __forceinline__ void lq_knots(SM &sm, const KArgs &a, int sid, int tid, int lane, int slot, int nthr,
+                                         int row0, int nq, int ntrig, int mp_from, float h,
+                                         int &bad_flag, PutA put_a, PutB put_b) {
+  constexpr int NX = 2 * ND, NU = ND, SLOTS = Shape<ND>::SLOTS;
+  for (int t = tid; t < ntrig * 8; t += nthr) {
+    const int k = row0 + t / 8, j = t % 8;
+    if (j < ND) sin_cos(sm.X[k][j], &sm.dX[k][ND + j], &sm.dX[k][j]);
+  }
+  __syncthreads();
+  const int half = (nq + 63) & ~63;   // threads of each half: whole wavefronts
+  {
+    const int t = tid < half ? tid : tid - half, k = row0 + t;
+    const bool mine = t < nq;
+    const Chain ch = load_uniform(&fresh_desc(a, sid)->chain);
+    float L[ND][ND] = {};   // (defined in every lane: not carried from one iteration to the next)
+    bool ok = true;
+    if (tid < half) {
+      if (mine) {
+        float cq[ND], sq[ND];
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+          cq[i] = sm.dX[k][i];
+          sq[i] = sm.dX[k][ND + i];
+        }
+        ok = fd_inertia<ND>(ch, cq, sq, L);
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+#pragma unroll
+          for (int j = 0; j <= i; ++j) sm.Lf[k][i * (i + 1) / 2 + j] = L[i][j];
+      }
+    } else if (tid < 2 * half && mine) {
+      float q[ND], qd[ND], cq[ND], sq[ND], b[ND];
+#pragma unroll
+      for (int i = 0; i < ND; ++i) {
+        q[i] = sm.X[k][i];
+        qd[i] = sm.X[k][ND + i];
+        cq[i] = sm.dX[k][i];
+        sq[i] = sm.dX[k][ND + i];
+      }
+      fd_bias<ND>(ch, q, cq, sq, qd, b);
+#pragma unroll
+      for (int i = 0; i < ND; ++i) sm.qdd[k][i] = b[i];
+    }
+    __syncthreads();
+    if (tid < half && mine) {
+      const CostWeights cw = load_weights(fresh_desc(a, sid));
+      float q[ND], qd[ND], u[ND], b[ND], qdd[ND];
+#pragma unroll
+      for (int i = 0; i < ND; ++i) {
+        q[i] = sm.X[k][i];
+        qd[i] = sm.X[k][ND + i];
+        u[i] = sm.U[k][i];
+        b[i] = sm.qdd[k][i];
+      }
+      fd_solve<ND>(L, u, b, qdd);
+#pragma unroll
+      for (int i = 0; i < ND; ++i) sm.qdd[k][i] = qdd[i];
+      float viol = 0.f, cost = 0.f;
+#pragma unroll
+      for (int i = 0; i < ND; ++i) {
+        const float e0 = (q[i] + h * qd[i]) - sm.X[k + 1][i];
+        const float e1 = (qd[i] + h * qdd[i]) - sm.X[k + 1][ND + i];
+        sm.e[k][i] = e0;
+        sm.e[k][ND + i] = e1;
+        viol += fabsf(e0) + fabsf(e1);
+      }
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        const float d = sm.X[k][i] - sm.xg[i];
+        cost += 0.5f * cw.Wq[i] * d * d;
+      }
+#pragma unroll
+      for (int i = 0; i < NU; ++i) cost += 0.5f * cw.Wr[i] * u[i] * u[i];
+      if (k >= mp_from) sm.mp0[k] = (double)cost + (double)a.mu * (double)viol;
+      if (!ok || !isfinite(viol) || !isfinite(cost)) bad_flag = 1;
+    }
+    __syncthreads();
+  }
+  const Chain ch = load_uniform(&fresh_desc(a, sid)->chain);
+  for (int t = slot; t < nq; t += SLOTS) {
+    const int k = row0 + t;
+    if (lane < NX) {
+      float q[ND], qd[ND], cq[ND], sq[ND], qdd[ND], col[ND];
+#pragma unroll
+      for (int i = 0; i < ND; ++i) {
+        q[i] = sm.X[k][i];
+        qd[i] = sm.X[k][ND + i];
+        cq[i] = sm.dX[k][i];
+        sq[i] = sm.dX[k][ND + i];
+        qdd[i] = sm.qdd[k][i];
+      }
+      id_tangent<ND>(ch, q, cq, sq, qd, qdd, lane, col);
+      float L[ND][ND];
+#pragma unroll
+      for (int i = 0; i < ND; ++i)
+#pragma unroll
+        for (int j = 0; j < ND; ++j) L[i][j] = (j <= i) ? sm.Lf[k][i * (i + 1) / 2 + j] : 0.f;
+      chol_solve<ND>(L, col);
+      put_a(k, col);
+      if (lane < ND) {
+        float mi[ND];
+#pragma unroll
+        for (int i = 0; i < ND; ++i) mi[i] = (i == lane) ? 1.f : 0.f;
+        chol_solve<ND>(L, mi);
+        put_b(k, mi);
+      }
+    }
+  }
+}
+
+// ---- Phase 6: the merit terms mp[i][k] of the trial knots (step candidate i, rows
+// row0 .. row0 + nst - 1), a thread each. Where two threads per trial knot exist
+// (HALVES: bias has space for kBlock / 2 of them), its dynamics' two halves run in
+// different wavefronts; otherwise a thread's one after the other, by the same
+// instructions, so that a solve's bits do not depend on the size of its workgroup.
+// 6 DoF N = 16 6.4 -> 5.0 us, 7 DoF N = 32 8.9 -> 7.4. Returns a number below n_alpha
+// in that many threads of wavefronts that are done early (for the terminal terms).
+template <int ND, bool TS, bool HALVES, class SM>
+__device__ __forceinline__ int ls_trials(SM &sm, const KArgs &a, int sid, const float *We,
+                                         const float (*pr)[4], float *bias, int tid, int nthr, int n_alpha, int row0,
+                                         int nst, float h) {
+  const int ntask = n_alpha * nst;
+  const Chain ch = load_uniform(&fresh_desc(a, sid)->chain);
+  const int half = (ntask + 63) & ~63;
+  const bool halves = HALVES && 2 * half <= nthr;
+  const bool second = halves && tid >= half;
+  const int step = halves ? half : nthr;
+  for (int t0 = 0; t0 < ntask; t0 += step) {
+    const int t = t0 + (second ? tid - half : tid);
+    const int i = t / nst, k = row0 + (t - i * nst);
+    const bool mine = t < ntask;
+    float q[ND] = {}, qd[ND] = {}, u[ND] = {}, L[ND][ND] = {}, b[ND] = {}, al = 0.f;
+    if (mine) {
+      al = sm.alpha[i];
+      float cq[ND], sq[ND];
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        q[j] = sm.X[k][j] + al * sm.dX[k][j];
+        qd[j] = sm.X[k][ND + j] + al * sm.dX[k][ND + j];
+        u[j] = sm.U[k][j] + al * sm.dU[k][j];
+      }
+#pragma unroll
+      for (int j = 0; j < ND; ++j) sin_cos(q[j], &sq[j], &cq[j]);
+      if (!second) fd_inertia<ND>(ch, cq, sq, L);
+      if (!halves || second) fd_bias<ND>(ch, q, cq, sq, qd, b);
+    }
+    if constexpr (HALVES) {
+      if (halves) {
+        if (mine && second) {
+#pragma unroll
+          for (int j = 0; j < ND; ++j) bias[t * ND + j] = b[j];
+        }
+        __syncthreads();
+        if (mine && !second) {
+#pragma unroll
+          for (int j = 0; j < ND; ++j) b[j] = bias[t * ND + j];
+        }
+      }
+    }
+    if (mine && !second) {
+      float qdd[ND];
+      fd_solve<ND>(L, u, b, qdd);
+      const CostWeights cw = load_weights(fresh_desc(a, sid));
+      float viol = 0.f, cost = 0.f;
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        const float x0 = sm.X[k + 1][j] + al * sm.dX[k + 1][j], x1 = sm.X[k + 1][ND + j] + al * sm.dX[k + 1][ND + j];
+        viol += fabsf((q[j] + h * qd[j]) - x0) + fabsf((qd[j] + h * qdd[j]) - x1);
+        const float d0 = q[j] - sm.xg[j], d1 = qd[j] - sm.xg[ND + j];
+        cost += 0.5f * cw.Wq[j] * d0 * d0 + 0.5f * cw.Wq[ND + j] * d1 * d1 + 0.5f * cw.Wr[j] * u[j] * u[j];
+      }
+      if constexpr (TS) {
+        float pt[3];
+        tip_position<ND>(ch, q, pt);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const float d = pt[c] - pr[k][c];
+          cost += 0.5f * We[c] * d * d;
+        }
+      }
+      sm.mp[i][k] = (double)cost + (double)a.mu * (double)viol;
+    }
+  }
+  const int i = halves ? tid - half : nthr - 1 - tid;
+  return i >= 0 ? i : n_alpha;
+}
+
 // ---- Task-space variant: the tip term of one knot, by the knot's lane group.
 // Tip position and Jacobian (lane j: one dual-number pass seeded on q_j), the
 // residual p(q) - pref and its cost (lane 0), then H = diag(Q_q + rho) +
 // J^T W J, its Cholesky factor L (column by column, lane i holding row i,
 // pivots broadcast through tq) and L^-1 (lane j forming column j by forward
-// substitution). x: the knot's state; Jt, pe, mt, tq, Lc, Li: its LDS rows.
+// substitution). cs: cos and sin of the knot's angles; Jt, pe, mt, tq, Lc, Li: its LDS rows.
 template <int ND>
-__device__ __forceinline__ void tip_factor(const Chain &ch, const float *x, const float *pr, const float *We,
+__device__ __forceinline__ void tip_factor(const Chain &ch, const float *cs, const float *pr, const float *We,
                                            const double *Qd, double rho, int lane, float (*Jt)[8], float *pe,
                                            double *mt, double *tq, double *Lc, double *Li, int &bad_flag) {
   if (lane < ND) {
-    dual<float> qv[ND], pt[3];
+    dual<float> cv[ND], sv[ND], pt[3];
 #pragma unroll
-    for (int i = 0; i < ND; ++i) qv[i] = dual<float>{x[i], i == lane ? 1.f : 0.f};
-    tip_position<ND>(ch, qv, pt);
+    for (int i = 0; i < ND; ++i) {
+      cv[i] = dual<float>{cs[i], i == lane ? -cs[ND + i] : 0.f};
+      sv[i] = dual<float>{cs[ND + i], i == lane ? cs[i] : 0.f};
+    }
+    tip_position<ND>(ch, cv, sv, pt);
 #pragma unroll
     for (int c = 0; c < 3; ++c) Jt[c][lane] = pt[c].d;
     if (lane == 0) {
@@ -1544,7 +1781,6 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
   // Only dereferenced by the task-space form, whose LDS holds it.
   PartTsSmem<ND> &ts = *reinterpret_cast<PartTsSmem<ND> *>(smem_raw + part_ts_offset<ND>());
   const SolveDesc &D = a.desc[sid];
-  const Chain &ch = D.chain;
   const int tid = threadIdx.x;
   const int lane0 = tid % G;
   const int slot0 = tid / G;
@@ -1649,78 +1885,23 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     // ================= 1. LQ at knots kq0..kq1 (the own knots and the one left of them).
     const int kq0 = max(kf - 1, 0), kq1 = min(kl, N - 2);
     const int nq = nloc > 0 ? kq1 - kq0 + 1 : 0;
-    for (int t = slot; t < nq; t += SLOTS) {
-      const int kk = kq0 + t, lq = kk - kf + 1;
-      if (lane == 0) {
-        float q[ND], qd[ND], u[ND], qdd[ND], L[ND][ND];
+    const int lt0 = kq0 - kf + 1;   // the first of their rows
+    const int nt = nloc > 0 ? (has_r ? nloc + 1 : nloc) - lt0 + 1 : 0;   // the rows from there on
+    lq_knots<ND>(sm, a, sid, tid, lane, slot, kBlock, lt0, nq, nt, 1, h, bad_flag, [&](int lq, const float *col) {
+      float *Ak = sm.A[lq];
 #pragma unroll
-        for (int i = 0; i < ND; ++i) {
-          q[i] = sm.X[lq][i];
-          qd[i] = sm.X[lq][ND + i];
-          u[i] = sm.U[lq][i];
-        }
-        const bool ok = forward_dynamics<ND>(ch, q, qd, u, qdd, L);
-#pragma unroll
-        for (int i = 0; i < ND; ++i) sm.qdd[lq][i] = qdd[i];
-#pragma unroll
-        for (int i = 0; i < ND; ++i)
-#pragma unroll
-          for (int j = 0; j <= i; ++j) sm.Lf[lq][i * (i + 1) / 2 + j] = L[i][j];
-        float viol = 0.f, cost = 0.f;
-#pragma unroll
-        for (int i = 0; i < ND; ++i) {
-          const float e0 = (q[i] + h * qd[i]) - sm.X[lq + 1][i];
-          const float e1 = (qd[i] + h * qdd[i]) - sm.X[lq + 1][ND + i];
-          sm.e[lq][i] = e0;
-          sm.e[lq][ND + i] = e1;
-          viol += fabsf(e0) + fabsf(e1);
-        }
-#pragma unroll
-        for (int i = 0; i < NX; ++i) {
-          const float d = sm.X[lq][i] - sm.xg[i];
-          cost += 0.5f * D.Wq[i] * d * d;
-        }
-#pragma unroll
-        for (int i = 0; i < NU; ++i) cost += 0.5f * D.Wr[i] * u[i] * u[i];
-        if (kk >= kf) sm.mp0[lq] = (double)cost + (double)a.mu * (double)viol;
-        if (!ok || !isfinite(viol) || !isfinite(cost)) bad_flag = 1;
+      for (int i = 0; i < ND; ++i) {
+        Ak[i * NX + lane] = (i == lane ? 1.f : 0.f) + (lane == ND + i ? h : 0.f);
+        Ak[(ND + i) * NX + lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
       }
-      wave_sync();
-      if (lane < NX) {
-        float q[ND], qd[ND], qdd[ND], col[ND];
+    }, [&](int lq, const float *mi) {
+      float *Bk = sm.B[lq];
 #pragma unroll
-        for (int i = 0; i < ND; ++i) {
-          q[i] = sm.X[lq][i];
-          qd[i] = sm.X[lq][ND + i];
-          qdd[i] = sm.qdd[lq][i];
-        }
-        id_tangent<ND>(ch, q, qd, qdd, lane, col);
-        float L[ND][ND];
-#pragma unroll
-        for (int i = 0; i < ND; ++i)
-#pragma unroll
-          for (int j = 0; j < ND; ++j) L[i][j] = (j <= i) ? sm.Lf[lq][i * (i + 1) / 2 + j] : 0.f;
-        chol_solve<ND>(L, col);
-        float *Ak = sm.A[lq];
-#pragma unroll
-        for (int i = 0; i < ND; ++i) {
-          Ak[i * NX + lane] = (i == lane ? 1.f : 0.f) + (lane == ND + i ? h : 0.f);
-          Ak[(ND + i) * NX + lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
-        }
-        if (lane < ND) {
-          float mi[ND];
-#pragma unroll
-          for (int i = 0; i < ND; ++i) mi[i] = (i == lane) ? 1.f : 0.f;
-          chol_solve<ND>(L, mi);
-          float *Bk = sm.B[lq];
-#pragma unroll
-          for (int i = 0; i < ND; ++i) {
-            Bk[i * NU + lane] = 0.f;
-            Bk[(ND + i) * NU + lane] = h * mi[i];
-          }
-        }
+      for (int i = 0; i < ND; ++i) {
+        Bk[i * NU + lane] = 0.f;
+        Bk[(ND + i) * NU + lane] = h * mi[i];
       }
-    }
+    });
     // Gradients at the knots kq0..kl, the initial residual, the terminal and
     // initial merit terms (owners of knot N - 1 and knot 0).
     const int lq0 = kq0 - kf + 1;
@@ -1750,11 +1931,9 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
     }
     if constexpr (TS) {
       // The tip terms and the factors L_k, L_k^-1 of the own knots and both halos.
-      const int lt0 = kf > 0 ? 0 : 1, lt1 = has_r ? nloc + 1 : nloc;
-      const int nt = nloc > 0 ? lt1 - lt0 + 1 : 0;
       for (int t = slot; t < nt; t += SLOTS) {
         const int lg = lt0 + t, kk = kof(lg);
-        tip_factor<ND>(ch, sm.X[lg], ts.pr[lg], (kk < N - 1) ? D.We : D.WeN, (kk < N - 1) ? D.Qd : D.QNd, rho,
+        tip_factor<ND>(D.chain, sm.dX[lg], ts.pr[lg], (kk < N - 1) ? D.We : D.WeN, (kk < N - 1) ? D.Qd : D.QNd, rho,
                        lane, ts.Jt[lg], ts.pe[lg], &ts.mt[lg], ts.tq[lg], ts.Lc[lg], ts.Li[lg], bad_flag);
       }
     }
@@ -1935,39 +2114,10 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
 
     // ================= 6. Line search over the own knots; partial merits summed over the parts.
     const int nst = (nloc > 0) ? min(kl, N - 2) - kf + 1 : 0;   // own knots with a control
-    const int ntask = n_alpha * max(nst, 0);
-    for (int t = tid; t < ntask; t += kBlock) {
-      const int i = t / nst, lg = 1 + (t - i * nst);
-      const float al = sm.alpha[i];
-      float q[ND], qd[ND], uu[ND], qdd[ND], L[ND][ND], xn[NX];
-#pragma unroll
-      for (int j = 0; j < ND; ++j) {
-        q[j] = sm.X[lg][j] + al * sm.dX[lg][j];
-        qd[j] = sm.X[lg][ND + j] + al * sm.dX[lg][ND + j];
-        uu[j] = sm.U[lg][j] + al * sm.dU[lg][j];
-      }
-#pragma unroll
-      for (int j = 0; j < NX; ++j) xn[j] = sm.X[lg + 1][j] + al * sm.dX[lg + 1][j];
-      forward_dynamics<ND>(ch, q, qd, uu, qdd, L);
-      float viol = 0.f, cost = 0.f;
-#pragma unroll
-      for (int j = 0; j < ND; ++j) {
-        viol += fabsf((q[j] + h * qd[j]) - xn[j]) + fabsf((qd[j] + h * qdd[j]) - xn[ND + j]);
-        const float d0 = q[j] - sm.xg[j], d1 = qd[j] - sm.xg[ND + j];
-        cost += 0.5f * D.Wq[j] * d0 * d0 + 0.5f * D.Wq[ND + j] * d1 * d1 + 0.5f * D.Wr[j] * uu[j] * uu[j];
-      }
-      if constexpr (TS) {
-        float pt[3];
-        tip_position<ND>(ch, q, pt);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const float d = pt[c] - ts.pr[lg][c];
-          cost += 0.5f * D.We[c] * d * d;
-        }
-      }
-      sm.mp[i][lg] = (double)cost + (double)a.mu * (double)viol;
-    }
-    for (int i = tid; i < n_alpha; i += kBlock) {
+    static_assert(kBlock / 2 * ND <= (K * SLOTS + 2) * NX * NX, "biases of the trial knots");
+    if (const int i = ls_trials<ND, TS, K == 1>(sm, a, sid, D.We, ts.pr, &sm.A[0][0], tid, kBlock, n_alpha, 1,
+                                                max(nst, 0), h);
+        i < n_alpha) {
       const float al = sm.alpha[i];
       double x0 = 0.0;
       if (nloc > 0 && kl == N - 1) {
@@ -1980,7 +2130,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
           float q[ND], pt[3];
 #pragma unroll
           for (int j = 0; j < ND; ++j) q[j] = sm.X[nloc][j] + al * sm.dX[nloc][j];
-          tip_position<ND>(ch, q, pt);
+          tip_position<ND>(D.chain, q, pt);
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             const float d = pt[c] - ts.pr[nloc][c];
@@ -2096,7 +2246,6 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
   // Only dereferenced by the task-space variant, whose LDS holds it.
   TsSmem<ND, KPT> &ts = *reinterpret_cast<TsSmem<ND, KPT> *>(smem_raw + ts_offset<ND, KPT, Real>());
   const SolveDesc &D = a.desc[sid];
-  const Chain &ch = D.chain;
   const int tid = threadIdx.x;
   const int lane0 = tid % G;
   const int slot0 = tid / G;
@@ -2260,83 +2409,27 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     }
     // ================= 1. LQ: dynamics, derivatives, defects, gradients.
     if (a.mode != kModeKkt) {
-      for (int k = slot; k < N - 1; k += SLOTS) {
-        if (lane == 0) {
-          float q[ND], qd[ND], u[ND], qdd[ND], L[ND][ND];
+      lq_knots<ND>(sm, a, sid, tid, lane, slot, nthr, 0, N - 1, N, 0, h, bad_flag, [&](int k, const float *col) {
+        if constexpr (kLong) {
 #pragma unroll
-          for (int i = 0; i < ND; ++i) {
-            q[i] = sm.X[k][i];
-            qd[i] = sm.X[k][ND + i];
-            u[i] = sm.U[k][i];
-          }
-          const bool ok = forward_dynamics<ND>(ch, q, qd, u, qdd, L);
-#pragma unroll
-          for (int i = 0; i < ND; ++i) sm.qdd[k][i] = qdd[i];
-#pragma unroll
-          for (int i = 0; i < ND; ++i)
-#pragma unroll
-            for (int j = 0; j <= i; ++j) sm.Lf[k][i * (i + 1) / 2 + j] = L[i][j];
-          float viol = 0.f, cost = 0.f;
-#pragma unroll
-          for (int i = 0; i < ND; ++i) {
-            const float e0 = (q[i] + h * qd[i]) - sm.X[k + 1][i];
-            const float e1 = (qd[i] + h * qdd[i]) - sm.X[k + 1][ND + i];
-            sm.e[k][i] = e0;
-            sm.e[k][ND + i] = e1;
-            viol += fabsf(e0) + fabsf(e1);
-          }
-#pragma unroll
-          for (int i = 0; i < NX; ++i) {
-            const float d = sm.X[k][i] - sm.xg[i];
-            cost += 0.5f * D.Wq[i] * d * d;
-          }
-#pragma unroll
-          for (int i = 0; i < NU; ++i) cost += 0.5f * D.Wr[i] * u[i] * u[i];
-          sm.mp0[k] = (double)cost + (double)a.mu * (double)viol;
-          if (!ok || !isfinite(viol) || !isfinite(cost)) bad_flag = 1;
+          for (int i = 0; i < ND; ++i) sm.Av[k][i][lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
         }
-        wave_sync();
-        if (lane < NX) {
-          float q[ND], qd[ND], qdd[ND], col[ND];
+        if (!kLong || a.mode == kModeLq) {
+          float *Ak = Ablk(k);
 #pragma unroll
           for (int i = 0; i < ND; ++i) {
-            q[i] = sm.X[k][i];
-            qd[i] = sm.X[k][ND + i];
-            qdd[i] = sm.qdd[k][i];
-          }
-          id_tangent<ND>(ch, q, qd, qdd, lane, col);
-          float L[ND][ND];
-#pragma unroll
-          for (int i = 0; i < ND; ++i)
-#pragma unroll
-            for (int j = 0; j < ND; ++j) L[i][j] = (j <= i) ? sm.Lf[k][i * (i + 1) / 2 + j] : 0.f;
-          chol_solve<ND>(L, col);
-          if constexpr (kLong) {
-#pragma unroll
-            for (int i = 0; i < ND; ++i) sm.Av[k][i][lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
-          }
-          if (!kLong || a.mode == kModeLq) {
-            float *Ak = Ablk(k);
-#pragma unroll
-            for (int i = 0; i < ND; ++i) {
-              Ak[i * NX + lane] = (i == lane ? 1.f : 0.f) + (lane == ND + i ? h : 0.f);
-              Ak[(ND + i) * NX + lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
-            }
-          }
-          if (lane < ND) {
-            float mi[ND];
-#pragma unroll
-            for (int i = 0; i < ND; ++i) mi[i] = (i == lane) ? 1.f : 0.f;
-            chol_solve<ND>(L, mi);
-            float *Bk = Bblk(k);
-#pragma unroll
-            for (int i = 0; i < ND; ++i) {
-              Bk[i * NU + lane] = 0.f;
-              Bk[(ND + i) * NU + lane] = h * mi[i];
-            }
+            Ak[i * NX + lane] = (i == lane ? 1.f : 0.f) + (lane == ND + i ? h : 0.f);
+            Ak[(ND + i) * NX + lane] = h * col[i] + (lane == ND + i ? 1.f : 0.f);
           }
         }
-      }
+      }, [&](int k, const float *mi) {
+        float *Bk = Bblk(k);
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+          Bk[i * NU + lane] = 0.f;
+          Bk[(ND + i) * NU + lane] = h * mi[i];
+        }
+      });
       for (int t = tid; t < N * G; t += nthr) {
         const int k = t / G, j = t % G;
         const float *W = (k < N - 1) ? D.Wq : D.Wn;
@@ -2356,7 +2449,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       if constexpr (TS) {
         // The tip terms and the factors L_k, L_k^-1 of every knot.
         for (int k = slot; k < N; k += SLOTS)
-          tip_factor<ND>(ch, sm.X[k], ts.pr[k], (k < N - 1) ? D.We : D.WeN, (k < N - 1) ? D.Qd : D.QNd, rho, lane,
+          tip_factor<ND>(D.chain, sm.dX[k], ts.pr[k], (k < N - 1) ? D.We : D.WeN, (k < N - 1) ? D.Qd : D.QNd, rho, lane,
                          ts.Jt[k], ts.pe[k], &ts.mt[k], ts.tq[k], ts.Lc[k], ts.Li[k], bad_flag);
       }
       if (a.mode == kModeLq) {
@@ -3209,39 +3302,15 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     if (clk) clk[5] = wall_clock64();
 
     // ================= 6. Line search over alpha_i = beta^-i (Eqs. (3), (7)).
-    const int ntask = n_alpha * (N - 1);
-    for (int t = tid; t < ntask; t += nthr) {
-      const int i = t / (N - 1), k = t - i * (N - 1);
-      const float al = sm.alpha[i];
-      float q[ND], qd[ND], uu[ND], qdd[ND], L[ND][ND], xn[NX];
-#pragma unroll
-      for (int j = 0; j < ND; ++j) {
-        q[j] = sm.X[k][j] + al * sm.dX[k][j];
-        qd[j] = sm.X[k][ND + j] + al * sm.dX[k][ND + j];
-        uu[j] = sm.U[k][j] + al * sm.dU[k][j];
-      }
-#pragma unroll
-      for (int j = 0; j < NX; ++j) xn[j] = sm.X[k + 1][j] + al * sm.dX[k + 1][j];
-      forward_dynamics<ND>(ch, q, qd, uu, qdd, L);
-      float viol = 0.f, cost = 0.f;
-#pragma unroll
-      for (int j = 0; j < ND; ++j) {
-        viol += fabsf((q[j] + h * qd[j]) - xn[j]) + fabsf((qd[j] + h * qdd[j]) - xn[ND + j]);
-        const float d0 = q[j] - sm.xg[j], d1 = qd[j] - sm.xg[ND + j];
-        cost += 0.5f * D.Wq[j] * d0 * d0 + 0.5f * D.Wq[ND + j] * d1 * d1 + 0.5f * D.Wr[j] * uu[j] * uu[j];
-      }
-      if constexpr (TS) {
-        float pt[3];
-        tip_position<ND>(ch, q, pt);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const float d = pt[c] - ts.pr[k][c];
-          cost += 0.5f * D.We[c] * d * d;
-        }
-      }
-      sm.mp[i][k] = (double)cost + (double)a.mu * (double)viol;
+    // (The biases go through the space of the A blocks, read for the last time in
+    // phase 2.)
+    float *kpt_bias = nullptr;
+    if constexpr (KPT == 1) {
+      static_assert(kBlock / 2 * ND <= BS::LB * NX * NX && BS::kLds, "biases of the trial knots");
+      kpt_bias = &sm.A[0][0];
     }
-    for (int i = tid; i < n_alpha; i += nthr) {
+    if (const int i = ls_trials<ND, TS, KPT == 1>(sm, a, sid, D.We, ts.pr, kpt_bias, tid, nthr, n_alpha, 0, N - 1, h);
+        i < n_alpha) {
       const float al = sm.alpha[i];
       float cost = 0.f, viol = 0.f;
       for (int j = 0; j < NX; ++j) {
@@ -3253,7 +3322,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
         float q[ND], pt[3];
 #pragma unroll
         for (int j = 0; j < ND; ++j) q[j] = sm.X[N - 1][j] + al * sm.dX[N - 1][j];
-        tip_position<ND>(ch, q, pt);
+        tip_position<ND>(D.chain, q, pt);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           const float d = pt[c] - ts.pr[N - 1][c];
