@@ -303,17 +303,17 @@ int gato_shift_warm_start(gato_batch *b, const int *d_slots, int n, void *hip_st
  * Serving launch context: the host side of one serving launch in native code,
  * for request loops that must not pay per-launch copies and allocations. A
  * context owns a HIP stream (default priority), a completion event, pinned
- * host staging and the device buffers of one launch of up to `capacity`
- * requests (1..M) running n_iters SQP iterations each.
+ * host memory for the inputs and outputs of one launch of up to `capacity`
+ * requests (1..M) running n_iters SQP iterations each, which the launch reads
+ * and writes itself, and device memory for its full plans.
  *   gato_serve_ctx_buffers: pointers to the pinned staging: inputs h_slots
  *     [capacity], h_xs [capacity][nx_max], h_goal [capacity][nu_max] (the
  *     caller writes requests 0..n_req-1 there), outputs h_x1
  *     [capacity][nx_max] (knot 1 of each new plan, the plant's next state
  *     under the plan), h_u0 [capacity][nu_max] (the first control) and
  *     h_stats [capacity][n_iters]. Any pointer argument may be NULL.
- *   gato_serve_ctx_submit: enqueues on the context's stream the copy of the
- *     first n_req inputs, gato_serve_step (with the given shift) and the copy
- *     of the outputs, then records the event. Returns at once. The outputs
+ *   gato_serve_ctx_submit: enqueues on the context's stream the serving step
+ *     of the first n_req inputs (with the given shift), then records the event. Returns at once. The outputs
  *     and the inputs' staging must not be touched until the query says done.
  *     Slots are checked on the host (GATO_EINVAL outside 0..M-1).
  *   gato_serve_ctx_query: 1 when the last submit has finished (outputs

@@ -803,9 +803,14 @@ int gato_get_trajectories(gato_batch *b, float *d_X, float *d_U) {
   return GATO_OK;
 }
 
-int gato_serve_step(gato_batch *b, int n_req, const int *d_slots, const float *d_xs, const float *d_goal,
-                    int n_iters, int shift, float *d_Xout, float *d_Uout, gato_solve_stats *d_stats,
-                    void *hip_stream) {
+}  // extern "C"
+
+namespace {
+
+// (x1, u0: the requests' next state and control, or null.)
+int serve_launch(gato_batch *b, int n_req, const int *d_slots, const float *d_xs, const float *d_goal, int n_iters,
+                 int shift, float *d_Xout, float *d_Uout, gato_solve_stats *d_stats, float *x1, float *u0,
+                 void *hip_stream) {
   if (!b) return fail(GATO_EINVAL, "batch is NULL");
   if (n_req < 1 || n_req > b->M) return fail(GATO_EINVAL, "n_req must be in 1..M");
   if (!d_slots || !d_xs || !d_goal) return fail(GATO_EINVAL, "slots, xs and goal must not be NULL");
@@ -826,6 +831,8 @@ int gato_serve_step(gato_batch *b, int n_req, const int *d_slots, const float *d
   a.shift = shift;
   a.Xout = d_Xout;
   a.Uout = d_Uout;
+  a.x1out = x1;
+  a.u0out = u0;
   hipStream_t st = hip_stream ? (hipStream_t)hip_stream : b->stream;
   hipError_t e = b->groups.size() == 1
                      ? gato::launch_sqp(b->groups[0].n, b->groups[0].kpt, b->p.schur_fp64 != 0, n_req, a, st)
@@ -834,11 +841,25 @@ int gato_serve_step(gato_batch *b, int n_req, const int *d_slots, const float *d
   return GATO_OK;
 }
 
+}  // namespace
+
+extern "C" {
+
+int gato_serve_step(gato_batch *b, int n_req, const int *d_slots, const float *d_xs, const float *d_goal,
+                    int n_iters, int shift, float *d_Xout, float *d_Uout, gato_solve_stats *d_stats,
+                    void *hip_stream) {
+  return serve_launch(b, n_req, d_slots, d_xs, d_goal, n_iters, shift, d_Xout, d_Uout, d_stats, nullptr, nullptr,
+                      hip_stream);
+}
+
 }  // extern "C"
 
 // A launch context of the serving loop: its own stream and completion event,
-// pinned host staging that the caller fills and reads in place, and the
-// device buffers of one launch.
+// pinned host memory that the caller fills and reads in place and the kernel reads
+// and writes directly (about 130 bytes per request: six copies around the kernel
+// took longer than it takes to read them over the bus; a request of one solve,
+// 7 DoF, N = 32, one iteration 171 -> 142 us), and the trajectories of one
+// launch.
 struct gato_serve_ctx {
   gato_batch *b = nullptr;
   int cap = 0, n_iters = 0, n_last = 0;
@@ -848,9 +869,7 @@ struct gato_serve_ctx {
   float *h_xs = nullptr, *h_goal = nullptr;      // pinned [cap][nx_max], [cap][nu_max]
   float *h_x1 = nullptr, *h_u0 = nullptr;        // pinned [cap][nx_max], [cap][nu_max]
   gato_solve_stats *h_stats = nullptr;           // pinned [cap][n_iters]
-  int *d_slots = nullptr;
-  float *d_xs = nullptr, *d_goal = nullptr, *d_X = nullptr, *d_U = nullptr;
-  gato_solve_stats *d_stats = nullptr;
+  float *d_X = nullptr, *d_U = nullptr;
 };
 
 extern "C" {
@@ -861,8 +880,7 @@ void gato_serve_ctx_destroy(gato_serve_ctx *c) {
   for (void *p : {(void *)c->h_slots, (void *)c->h_xs, (void *)c->h_goal, (void *)c->h_x1, (void *)c->h_u0,
                   (void *)c->h_stats})
     if (p) (void)hipHostFree(p);
-  for (void *p : {(void *)c->d_slots, (void *)c->d_xs, (void *)c->d_goal, (void *)c->d_X, (void *)c->d_U,
-                  (void *)c->d_stats})
+  for (void *p : {(void *)c->d_X, (void *)c->d_U})
     if (p) (void)hipFree(p);
   if (c->done) (void)hipEventDestroy(c->done);
   if (c->stream) (void)hipStreamDestroy(c->stream);
@@ -889,12 +907,8 @@ int gato_serve_ctx_create(gato_batch *b, int capacity, int n_iters, gato_serve_c
   if (e == hipSuccess) e = hipHostMalloc((void **)&c->h_u0, cap * nu * sizeof(float), hipHostMallocDefault);
   if (e == hipSuccess)
     e = hipHostMalloc((void **)&c->h_stats, cap * n_iters * sizeof(gato_solve_stats), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipMalloc((void **)&c->d_slots, cap * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc((void **)&c->d_xs, cap * nx * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc((void **)&c->d_goal, cap * nu * sizeof(float));
   if (e == hipSuccess) e = hipMalloc((void **)&c->d_X, cap * N * nx * sizeof(float));
   if (e == hipSuccess) e = hipMalloc((void **)&c->d_U, cap * (N - 1) * nu * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc((void **)&c->d_stats, cap * n_iters * sizeof(gato_solve_stats));
   if (e != hipSuccess) {
     gato_serve_ctx_destroy(c);
     return hip_fail(e, "serve context set-up");
@@ -902,6 +916,9 @@ int gato_serve_ctx_create(gato_batch *b, int capacity, int n_iters, gato_serve_c
   std::memset(c->h_slots, 0, cap * sizeof(int));
   std::memset(c->h_xs, 0, cap * nx * sizeof(float));
   std::memset(c->h_goal, 0, cap * nu * sizeof(float));
+  std::memset(c->h_x1, 0, cap * nx * sizeof(float));
+  std::memset(c->h_u0, 0, cap * nu * sizeof(float));
+  std::memset(c->h_stats, 0, cap * n_iters * sizeof(gato_solve_stats));
   *out = c;
   return GATO_OK;
 }
@@ -922,26 +939,15 @@ int gato_serve_ctx_submit(gato_serve_ctx *c, int n_req, int shift) {
   if (!c) return fail(GATO_EINVAL, "context is NULL");
   if (n_req < 1 || n_req > c->cap) return fail(GATO_EINVAL, "n_req must be in 1..capacity");
   gato_batch *b = c->b;
-  const size_t nx = 2 * (size_t)b->n_max, nu = (size_t)b->n_max, N = (size_t)b->N_max, R = (size_t)n_req;
   for (int r = 0; r < n_req; ++r)
     if (c->h_slots[r] < 0 || c->h_slots[r] >= b->M) return fail(GATO_EINVAL, "slot outside 0..M-1");
   hipStream_t s = c->stream;
-  hipError_t e = hipMemcpyAsync(c->d_slots, c->h_slots, R * sizeof(int), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(c->d_xs, c->h_xs, R * nx * sizeof(float), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(c->d_goal, c->h_goal, R * nu * sizeof(float), hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(serve inputs)");
-  const int rc = gato_serve_step(b, n_req, c->d_slots, c->d_xs, c->d_goal, c->n_iters, shift, c->d_X, c->d_U,
-                                 c->d_stats, s);
+  // In: slots, measured states and goals; out: the plant's next state x_1 and the
+  // control u_0 of every request, and its statistics.
+  const int rc = serve_launch(b, n_req, c->h_slots, c->h_xs, c->h_goal, c->n_iters, shift, c->d_X, c->d_U, c->h_stats,
+                              c->h_x1, c->h_u0, s);
   if (rc != GATO_OK) return rc;
-  // The plant's next state x_1 and the control u_0 of every request, and its statistics.
-  e = hipMemcpy2DAsync(c->h_x1, nx * sizeof(float), c->d_X + nx, N * nx * sizeof(float), nx * sizeof(float), R,
-                       hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess)
-    e = hipMemcpy2DAsync(c->h_u0, nu * sizeof(float), c->d_U, (N - 1) * nu * sizeof(float), nu * sizeof(float), R,
-                         hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->h_stats, c->d_stats, R * c->n_iters * sizeof(gato_solve_stats), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipEventRecord(c->done, s);
+  const hipError_t e = hipEventRecord(c->done, s);
   if (e != hipSuccess) return hip_fail(e, "serve outputs");
   c->n_last = n_req;
   return GATO_OK;

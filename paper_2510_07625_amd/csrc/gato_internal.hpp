@@ -80,10 +80,12 @@ struct KArgs {
   unsigned long long *clk;    // optional [M][iters][8] phase timestamps (profiling)
   // Serving: xs, goal and stats indexed by workgroup (request) instead of
   // solve; the warm start is shifted by `shift` knots when it is loaded; the
-  // final trajectories are also gathered per request into Xout / Uout.
+  // final trajectories are also gathered per request into Xout / Uout, the state
+  // x_1 and the control u_0 into x1out / u0out (a launch context's pinned memory).
   int by_block;
   int shift;
   float *Xout, *Uout;
+  float *x1out, *u0out;
   // Split launch (split = 4 or 2 parts per long solve, 0: none): `order` entries
   // carry the part in bits 24..31 and the solve in bits 0..23; the parts of a
   // solve exchange through `xch` under tags of this launch's `epoch`

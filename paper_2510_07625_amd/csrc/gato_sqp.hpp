@@ -29,7 +29,8 @@
 //      runs the standard arrangement.)
 //   5. Step dZ = -G^-1 (g - C^T lambda) (Eq. (4)).
 //   6. Line search (Eqs. (3), (7)): thread (alpha, knot) evaluates one trial
-//      knot, or one thread each half of its dynamics; a fixed-order reduction gives each candidate's merit.
+//      knot, or one thread each half of its dynamics; a fixed-order reduction
+//      gives each candidate's merit.
 // The Schur rows, gamma~, the block inverses, the PCG vectors and its inner
 // products use Real (double; float for the all-FP32 variant). Dynamics and the
 // line search's trial points use float; the explicit preconditioner blocks of
@@ -575,10 +576,10 @@ __device__ __forceinline__ void block_sum(double (*red)[3][kBlock / 64], int &bu
 // (z, then v) is published per product. Rows that do not exist are zero and the
 // knots beyond the ends are zero rows of the buffers, so the loop has no masks.
 // Measured against P and S~ applied one after the other (us per PCG iteration,
-// MI355X): 7 DoF N = 32, 256 solves 1.49 -> 0.90; N = 64 3.07 -> 1.37 (two
+// MI355X): 7 DoF N = 32, 256 solves 1.49 -> 0.87; N = 64 3.07 -> 1.29 (two
 // knots per lane group: the A rows in FP64 and no spills in the loop); 6 DoF
-// N = 8 0.94 -> 0.55; tip tracking 7 DoF N = 32 1.54 -> 1.01. The loop of one
-// knot per lane group has 128 VALU instructions (237), 84 of them the products.
+// N = 8 0.94 -> 0.50; tip tracking 7 DoF N = 32 1.54 -> 1.00. The loop of one
+// knot per lane group has 117 VALU instructions (237), 72 of them the products.
 
 // Two sums over the workgroup through the matrix cores: three v_mfma_f64_4x4x4
 // (lane = i + 4 block + 16 k for A, j + 4 block + 16 k for B, j + 4 block + 16 i
@@ -858,7 +859,7 @@ struct NoExchange {
 // PIPE = false (tip tracking): u and w from r itself and a barrier more for the
 // sums. The tip systems are conditioned worse (kappa(P S~) about 2e4): there the
 // pipelined recurrences stop converging near a tolerance of 1e-8 (the cap of
-// 2000 iterations instead of about 300), for 0.96 against 1.01 us per iteration.
+// 2000 iterations instead of about 300), for 0.96 against 1.00 us per iteration.
 // The loop's time is the latency of its two exchanges through LDS next to the
 // two wavefronts' FMAs, so everything that hangs on the sums (scalars, stopping
 // test) sits where another product is under way; the test is taken after the
@@ -3386,10 +3387,12 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       if (j < NX) {
         a.X[xoff + (size_t)k * a.nx_max + j] = sm.X[k][j];
         if (a.Xout) a.Xout[rxo + (size_t)k * a.nx_max + j] = sm.X[k][j];
+        if (a.x1out && k == 1) a.x1out[(size_t)blockIdx.x * a.nx_max + j] = sm.X[k][j];
       }
       if (k < N - 1 && j < NU) {
         a.U[uoff + (size_t)k * a.nu_max + j] = sm.U[k][j];
         if (a.Uout) a.Uout[ruo + (size_t)k * a.nu_max + j] = sm.U[k][j];
+        if (a.u0out && k == 0) a.u0out[(size_t)blockIdx.x * a.nu_max + j] = sm.U[k][j];
       }
     }
 #pragma unroll
