@@ -88,12 +88,12 @@ def profiled_kernel(path):
 
 
 # LDS bytes the FP64 one-knot-per-group PCG iteration moves per lane (16 lanes
-# per knot, idle lanes included): one FP64 entry of each of the four neighbour
-# vectors (the two of the S~ product and the two of the preconditioner's
-# off-diagonal product; the other entries arrive by row broadcasts from the
-# lanes that read them), the two per-wavefront partial vectors of the
-# reduction (8 FP64 each), and the four FP64 values each lane publishes.
-LDS_BYTES_PER_LANE_PCG_ITER = 4 * 8 + 2 * 8 * 8 + 4 * 8
+# per knot, idle lanes included): at each of the two off-diagonal products three
+# FP64 entries of the neighbour knots' vectors (the other entries arrive by row
+# broadcasts from the lanes that read them), four FP64 partial sums of the
+# reduction, and the three FP64 values each lane writes (both published vectors
+# and its slot of the partial sums).
+LDS_BYTES_PER_LANE_PCG_ITER = 2 * 3 * 8 + 4 * 8 + 3 * 8
 
 
 def lds_report(g, kernel_ms, pcg_iters_launch, M=256, N=32):
@@ -107,8 +107,8 @@ def lds_report(g, kernel_ms, pcg_iters_launch, M=256, N=32):
     return dict(bytes_per_launch_pcg=bytes_launch, achieved_GBps=achieved / 1e9, peak_GBps=peak / 1e9,
                 frac=achieved / peak, peak_bytes_per_clk_cu=dict(distinct=per_clk0, broadcast16=per_clk1),
                 peak_GBps_by_pattern=dict(distinct=per_s0 / 1e9, broadcast16=per_s1 / 1e9),
-                model="PCG iterations x N knots x 16 lanes x (4 neighbour-vector FP64 entries + 2 x 8 partials "
-                      "+ 4 published FP64) bytes")
+                model="PCG iterations x N knots x 16 lanes x (2 x 3 neighbour-vector FP64 entries + 4 partials "
+                      "+ 3 written FP64) bytes")
 
 
 def _pcts(ms):

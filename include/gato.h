@@ -313,8 +313,9 @@ int gato_shift_warm_start(gato_batch *b, const int *d_slots, int n, void *hip_st
  *     under the plan), h_u0 [capacity][nu_max] (the first control) and
  *     h_stats [capacity][n_iters]. Any pointer argument may be NULL.
  *   gato_serve_ctx_submit: enqueues on the context's stream the serving step
- *     of the first n_req inputs (with the given shift), then records the event. Returns at once. The outputs
- *     and the inputs' staging must not be touched until the query says done.
+ *     of the first n_req inputs (with the given shift), then records the event.
+ *     Returns at once. The outputs and the inputs must not be touched until the
+ *     query says done.
  *     Slots are checked on the host (GATO_EINVAL outside 0..M-1).
  *   gato_serve_ctx_query: 1 when the last submit has finished (outputs
  *     valid), 0 while it runs, negative on a device error.
