@@ -837,6 +837,19 @@ __device__ __forceinline__ void invert_knot(int lane, bool first, const double *
   for (int c = 0; c < NX; ++c) Pd[c] = lane < NX ? thr[c] : 0.0;
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
+// Where u and w are formed from r itself (tip tracking, pcg_long), gamma goes on
+// falling for as long as the tolerance asks for it (the pipelined recurrences stall
+// some twenty orders of magnitude below its start). Those loops stop here, where
+// the scalars are still inside FP64's range; a tolerance further down is reported
+// as not reached.
+constexpr double kGammaMin = 1e-280;
+
 // What a solve on one workgroup exchanges with others: nothing.
 struct NoExchange {
   static constexpr bool on = false;
@@ -959,11 +972,14 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
   for (int p = 0; p < K; ++p) vs[p] = vp[p] = 0.0;
   // rg = 1 / gamma_prev and cga = 1 / (gamma_prev alpha_prev) = d_prev /
   // gamma_prev^2 (d: alpha's divisor) turn beta and alpha into two independent
-  // reciprocals.
+  // reciprocals. (Squares of gamma, which only the pipelined loop keeps in range; the
+  // other one has ra = 1 / alpha_prev, for as many operations behind the sums.)
   double rg = 0.0, cga = 0.0;
   int its = 0;
   if constexpr (!PIPE) {
     static_assert(!X::on, "the parts of a split solve run the pipelined loop");
+    const double limit = uniform(stop < kGammaMin ? kGammaMin : stop);
+    double ra = 0.0;
     for (;;) {
       double pr = 0.0, pw = 0.0;
       each([&](int p) {
@@ -976,12 +992,12 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
       double gma, dlt;
       sums.get(gma, dlt);
       const double beta = gma * rg;
-      const double d = dlt - gma * gma * cga;
+      const double d = dlt - beta * (gma * ra);
       rg = rcp_pcg(gma);
       const double alpha = gma * rcp_pcg(d);
-      cga = d * (rg * rg);
+      ra = d * rg;
       capped = gma > stop;
-      if (!__builtin_amdgcn_readfirstlane((int)capped) || its >= max_it) break;
+      if (!__builtin_amdgcn_readfirstlane((int)(gma > limit)) || its >= max_it) break;
       each([&](int p) {
         vs[p] = w[p] + beta * vs[p];
         r[p] -= alpha * vs[p];
@@ -992,6 +1008,9 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
         vp[p] = u[p] + beta * vp[p];
         lam[p] += alpha * vp[p];
       });
+      // (Before the barrier, where the wavefront waits anyway: behind it, with one
+      // knot per lane, 1.04 against 1.01 us per iteration.)
+      if constexpr (K == 1) __builtin_amdgcn_sched_barrier(0);
       __syncthreads();
       read(pb.z);
       off(y);
@@ -1073,17 +1092,12 @@ __device__ __forceinline__ int pcg_half_sweeps(PcgBufs<ND, K> &pb, int tid, int 
 
 // The same for four knots per lane group, whose registers hold D^-1 and the
 // vectors but not the rows of O (OffLds): one knot at a time between barriers, so
-// that only one knot's entries of A are in registers, and the arrangement with
-// u and w from r (two vectors fewer, one barrier more). na: knots per lane of
-// this wavefront that exist. Bound by the conversions and FMAs of 680 VALU
+// that only one knot's entries of A are in registers (the loop's scalars in scalar
+// registers), and the arrangement with u and w from r (two vectors fewer, one
+// barrier more). na: knots per lane of this wavefront that exist. Bound by the conversions and FMAs of 680 VALU
 // instructions per wavefront and iteration. 6 DoF N = 128, 512 solves: 17.4 us per
 // iteration with all rows read back through L2 (and D^-1 rows in FP32, 5-8% more
 // iterations), 3.3 us; the call 15.1 -> 3.0 ms.
-// The loop's scalars, the same in every lane, are kept in scalar registers.
-__device__ __forceinline__ double uniform(double v) {
-  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
-                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
-}
 template <int ND, int K, class Off>
 __device__ __forceinline__ int pcg_long(PcgBufs<ND, K> &pb, int tid, int lane, int slot, int na, const Off &o,
                                         const double (&Pd)[K][2 * ND], const double (&gam)[K], double (&r)[K],
@@ -1118,11 +1132,11 @@ __device__ __forceinline__ int pcg_long(PcgBufs<ND, K> &pb, int tid, int lane, i
   __syncthreads();
   sums.read(pb.red, tid);
   sums.get(eta, unused);
-  const double stop = uniform(tol * tol * eta);
+  const double stop = uniform(tol * tol * eta), limit = stop < kGammaMin ? kGammaMin : stop;
   double vs[K], vp[K];
 #pragma unroll
   for (int p = 0; p < K; ++p) u[p] = w[p] = vs[p] = vp[p] = 0.0;
-  double rg = 0.0, cga = 0.0, alpha = 0.0, beta = 0.0;
+  double rg = 0.0, ra = 0.0, alpha = 0.0, beta = 0.0;
   // (The first pass only forms u = P r and w = S~ u.)
   for (int its = -1;;) {
     each([&](int p, int k) {
@@ -1151,14 +1165,15 @@ __device__ __forceinline__ int pcg_long(PcgBufs<ND, K> &pb, int tid, int lane, i
     sums.read(pb.red, tid);
     double gma, dlt;
     sums.get(gma, dlt);
-    beta = uniform(gma * rg);
-    const double d = dlt - gma * gma * cga;
+    const double bt = gma * rg;
+    beta = uniform(bt);
+    const double d = dlt - bt * (gma * ra);
     const double rgm = rcp_pcg(gma);
     rg = uniform(rgm);
     alpha = uniform(gma * rcp_pcg(d));
-    cga = uniform(d * (rgm * rgm));
+    ra = uniform(d * rgm);
     capped = gma > stop;
-    if (!__builtin_amdgcn_readfirstlane((int)capped) || its >= max_it) return its;
+    if (!__builtin_amdgcn_readfirstlane((int)(gma > limit)) || its >= max_it) return its;
   }
 }
 
