@@ -48,7 +48,8 @@ inline hipError_t cooperative_fits(const void *f, int grid) {
   return cap >= grid ? hipSuccess : hipErrorCooperativeLaunchTooLarge;
 }
 
-// Launches the closed-loop plant step (RK4, one 16-lane group per instance).
+// Launches the closed-loop plant step (RK4; a 16-lane group per instance, or a thread
+// where there are very many).
 hipError_t launch_plant(const PlantArgs &a, hipStream_t s);
 
 // Fills n doubles with v.

@@ -1,6 +1,7 @@
 // Plant of closed-loop studies: the robot integrated with classical RK4 on its
 // continuous dynamics (the simulations of Sec. IV-E run the plant at 1 kHz with
-// RK4), one 16-lane group per instance, FP64 arithmetic on FP32 states.
+// RK4), one 16-lane group per instance (for very many instances one thread,
+// launch_plant), FP64 arithmetic on FP32 states.
 //
 // A step is one serial chain of 4 substeps forward dynamics, so its time is one
 // evaluation's latency. Lane j < n runs the recursive Newton-Euler pass for unit
@@ -243,6 +244,74 @@ __global__ __launch_bounds__(64) void plant_kernel(PlantArgs a) {
   if (lane == 0) a.status[r] = (bad & 0xffffull) ? GATO_ST_NONFINITE : 0u;
 }
 
+// The same with one thread per instance: about twice the latency, but a sixteenth of
+// the wavefronts.
+template <int ND>
+__device__ __forceinline__ bool plant_rk4_thread(const Chain &ch, double h, int substeps, const float *x,
+                                                 const float *tau, float *xn) {
+  constexpr int NX = 2 * ND;
+  double y[NX], k[NX], acc[NX], z[NX], u[ND], L[ND][ND];
+#pragma unroll
+  for (int i = 0; i < NX; ++i) y[i] = (double)x[i];
+#pragma unroll
+  for (int i = 0; i < ND; ++i) u[i] = (double)tau[i];
+  const double d = h / substeps;
+  bool fine = true;
+  for (int s = 0; s < substeps; ++s) {
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      acc[i] = 0.0;
+      z[i] = y[i];
+    }
+#pragma unroll 1
+    for (int st = 0; st < 4; ++st) {
+#pragma unroll
+      for (int i = 0; i < ND; ++i) k[i] = z[ND + i];
+      fine = forward_dynamics<ND, double>(ch, z, z + ND, u, k + ND, L) && fine;
+      const double wt = st == 0 || st == 3 ? 1.0 : 2.0, dt = st == 2 ? d : 0.5 * d;
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        acc[i] += wt * k[i];
+        z[i] = y[i] + dt * k[i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NX; ++i) y[i] += d / 6.0 * acc[i];
+  }
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+    xn[i] = (float)y[i];
+    fine = fine && isfinite(y[i]);
+  }
+  return fine;
+}
+
+__global__ __launch_bounds__(64) void plant_thread_kernel(PlantArgs a) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= a.n) return;
+  const int sid = a.slots ? a.slots[r] : r;
+  if (sid < 0 || sid >= a.M) {
+    a.status[r] = GATO_ST_NONFINITE;
+    return;
+  }
+  Chain ch = a.desc[sid].chain;
+  if (a.fext) {
+    for (int c = 0; c < 3; ++c) ch.fe[c] = a.fext[(size_t)r * 3 + c];
+    ch.has_fe = (ch.fe[0] != 0.f || ch.fe[1] != 0.f || ch.fe[2] != 0.f) && ch.model == 0;
+  }
+  const float *x = a.x + (size_t)r * a.nx_max;
+  const float *tau = a.tau + (size_t)r * a.nu_max;
+  float *xn = a.xn + (size_t)r * a.nx_max;
+  bool fine = false;
+  switch (ch.n) {
+    case 3: fine = plant_rk4_thread<3>(ch, a.h, a.substeps, x, tau, xn); break;
+    case 6: fine = plant_rk4_thread<6>(ch, a.h, a.substeps, x, tau, xn); break;
+    case 7: fine = plant_rk4_thread<7>(ch, a.h, a.substeps, x, tau, xn); break;
+    default: break;
+  }
+  a.status[r] = fine ? 0u : GATO_ST_NONFINITE;
+}
+
 // Tip position of every knot of every solve, one thread per (solve, knot);
 // zero beyond a solve's horizon and for the double-integrator model.
 __global__ __launch_bounds__(256) void tip_kernel(const SolveDesc *desc, int M, int N_max, int nx_max,
@@ -394,8 +463,16 @@ hipError_t launch_tips(const SolveDesc *desc, int M, int N_max, int nx_max, cons
   return hipGetLastError();
 }
 
+// Lane groups as long as their rounds of the device (256 CUs of four wavefronts of
+// four groups) take less time than the one round of a thread per instance. us per
+// call of 10 substeps, groups / threads, at 4096, 8192, 12288 and 65536 instances:
+// 3 DoF 53 / 81, 90 / 82, 128 / 82, 609 / 96; 6 DoF 88 / 171, 161 / 172, 235 / 172,
+// 1125 / 206; 7 DoF 107 / 205, 197 / 206, 289 / 209, 1343 / 251. (nu_max: the
+// batch's largest robot, which sets the time.)
 hipError_t launch_plant(const PlantArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(plant_kernel, dim3((a.n + 3) / 4), dim3(64), 0, s, a);
+  const int rounds = a.nu_max <= 3 ? 1 : 2;
+  if (a.n > rounds * 4096) hipLaunchKernelGGL(plant_thread_kernel, dim3((a.n + 63) / 64), dim3(64), 0, s, a);
+  else hipLaunchKernelGGL(plant_kernel, dim3((a.n + 3) / 4), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
