@@ -604,7 +604,8 @@ int launch_groups(gato_batch *b, gato::KArgs a, hipStream_t s, bool allow_split 
     }
     return GATO_OK;
   }
-  if (use_mixed(b)) {
+  // (Caller-given QP data: the mixed-shape kernel has no long solves of that kind.)
+  if (use_mixed(b) && a.mode != gato::kModeKkt) {
     for (int q = 0; split && q < 2; ++q) {
       if (b->grid_split_all[q] <= b->M) continue;
       as.split = q == 0 ? 4 : 2;

@@ -689,17 +689,15 @@ struct OffLds {
     const int km = min(max(slot + p * Shape<ND>::SLOTS - 1, 0), N - 2);
     const double g = xl * qi;
     double t = 0.0;
+    const float *ar = FULL ? full + ((size_t)km * NX + min(lane, NX - 1)) * NX
+                           : Av[km][lane >= ND && lane < NX ? lane - ND : 0];
+    float c[NX];
+#pragma unroll
+    for (int m = 0; m < NX; ++m) c[m] = ar[m];
+    row_dot1_f<NX>(t, g, c);
     if constexpr (FULL) {
-      const float *ar = full + ((size_t)km * NX + min(lane, NX - 1)) * NX;
-#pragma unroll 1
-      for (int m = 0; m < NX; ++m) t += (double)ar[m] * __shfl(g, m, 16);
       return t;
     } else {
-      const float *ar = Av[km][lane >= ND && lane < NX ? lane - ND : 0];
-      float c[NX];
-#pragma unroll
-      for (int m = 0; m < NX; ++m) c[m] = ar[m];
-      row_dot1_f<NX>(t, g, c);
       const double up = dpp<0x100 + ND>(g);   // the entry of lane + ND
       return lane < ND ? fma(h, up, g) : t;
     }
@@ -707,13 +705,14 @@ struct OffLds {
   __device__ __forceinline__ double col(int p, double xr) const {
     constexpr int NX = 2 * ND;
     const int kc = min(slot + p * Shape<ND>::SLOTS, N - 2), l = min(lane, NX - 1);
+    float c[NX];
     if constexpr (FULL) {
+#pragma unroll
+      for (int m = 0; m < NX; ++m) c[m] = full[((size_t)kc * NX + m) * NX + l];
       double t = 0.0;
-#pragma unroll 1
-      for (int m = 0; m < NX; ++m) t += (double)full[((size_t)kc * NX + m) * NX + l] * __shfl(xr, m, 16);
+      row_dot1_f<NX>(t, xr, c);
       return qown[p] * t;
     } else {
-      float c[NX];
 #pragma unroll
       for (int m = 0; m < ND; ++m) c[ND + m] = Av[kc][m][l];
       const double dn = dpp<0x110 + ND>(xr);   // the entry of lane - ND
@@ -2250,7 +2249,10 @@ __device__ __attribute__((always_inline)) inline void sqp_solve_part(const KArgs
   }
 }
 
-template <int ND, int KPT, class Real, bool TS = false, bool SPLIT = false>
+// KKT (four knots per lane group, FP64): the kernels of caller-given QP data, whose
+// products read whole A blocks. They are kernels of their own for their registers:
+// in one with the Euler step's products, those ran 8% slower (7 DoF, N = 128).
+template <int ND, int KPT, class Real, bool TS = false, bool SPLIT = false, bool KKT = false>
 __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, int sid, int part, char *smem_raw) {
   using Sh = Shape<ND>;
   constexpr int NX = Sh::NX, NU = Sh::NU, G = Sh::G, SLOTS = Sh::SLOTS;
@@ -2258,6 +2260,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
   constexpr bool kHalf = half_sweeps<Real, KPT>();
   constexpr bool kLong = long_form<Real, KPT>();
   using SM = Smem<ND, KPT, Real, TS>;
+  if constexpr (kLong) __builtin_assume((a.mode == kModeKkt) == KKT);
   SM &sm = *reinterpret_cast<SM *>(smem_raw);
   // Only dereferenced by the task-space variant, whose LDS holds it.
   TsSmem<ND, KPT> &ts = *reinterpret_cast<TsSmem<ND, KPT> *>(smem_raw + ts_offset<ND, KPT, Real>());
@@ -2544,7 +2547,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       double Pd[KPT][NX];                                        // row of D_k^-1
       double gam[KPT], res[KPT], qown[KPT];
       // The A blocks as they are.
-      const float *full = TS || a.mode == kModeKkt ? Ablk(0) : nullptr;
+      const float *full = TS || (kLong ? KKT : a.mode == kModeKkt) ? Ablk(0) : nullptr;
       if constexpr (kLong) {
         for (int t = tid; t < PcgBufs<ND, KPT>::KH * G; t += nthr) (&sm.pcg.z[0][0])[t] = (&sm.pcg.v[0][0])[t] = 0.0;
         if (tid < 64) sm.pcg.red[tid] = 0.0;
@@ -2610,13 +2613,11 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
       };
       using std::integral_constant;
       const double q0 = lane < NX ? sm.Qi[lane] : 0.0;
-      const OffLds<ND, KPT, true> off_full{nullptr, full, qown, q0, 0.0, lane, slot, N};
       if constexpr (kLong) {
         int na = 0;
         for (int p = 0; p < KPT; ++p) na += slot_w + p * SLOTS < N ? 1 : 0;
-        const OffLds<ND, KPT, false> off{sm.Av, nullptr, qown, q0, (double)h, lane, slot, N};
-        its = full ? pcg_long<ND, KPT>(sm.pcg, tid, lane, slot, na, off_full, Pd, gam, res, lam, a.pcg_tol, max_it, capped)
-                   : pcg_long<ND, KPT>(sm.pcg, tid, lane, slot, na, off, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
+        const OffLds<ND, KPT, KKT> off{sm.Av, full, qown, q0, (double)h, lane, slot, N};
+        its = pcg_long<ND, KPT>(sm.pcg, tid, lane, slot, na, off, Pd, gam, res, lam, a.pcg_tol, max_it, capped);
       } else if (TS || full) {
         double Ac[KPT][NX];
 #pragma unroll
@@ -2648,9 +2649,8 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
           double d = -qown[p] * ((double)sm.qg[k][lane] - lam[p]);
           const double *ln = sm.pcg.z[k + 2];
           if constexpr (kLong) {
-            const OffLds<ND, KPT, false> off{sm.Av, nullptr, qown, q0, (double)h, lane, slot, N};
-            if (full) off_full.add_col(p, d, ln[lane], 0.0);
-            else off.add_col(p, d, ln[lane], 0.0);
+            const OffLds<ND, KPT, KKT> off{sm.Av, full, qown, q0, (double)h, lane, slot, N};
+            off.add_col(p, d, ln[lane], 0.0);
           } else if (TS || full) {
             if (k < N - 1) {
               const float *A = Ablk(k);
@@ -3418,7 +3418,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
   }
 }
 
-template <int ND, int KPT, class Real, bool TS = false, bool SPLIT = false>
+template <int ND, int KPT, class Real, bool TS = false, bool SPLIT = false, bool KKT = false>
 __global__ __launch_bounds__(kBlock) void sqp_kernel(KArgs a) {
   constexpr size_t kOne = smem_bytes<ND, KPT, Real, TS>();
   constexpr size_t kPart = SPLIT && sizeof(Real) == 8 ? long_part_bytes<ND>() : 0;
@@ -3434,7 +3434,7 @@ __global__ __launch_bounds__(kBlock) void sqp_kernel(KArgs a) {
     }
   }
   if (sid < 0 || sid >= a.M) return;   // a caller-provided slot out of range: nothing to do
-  sqp_solve<ND, KPT, Real, TS, SPLIT>(a, sid, part, smem);
+  sqp_solve<ND, KPT, Real, TS, SPLIT, KKT>(a, sid, part, smem);
 }
 
 // Mixed-shape kernel: every workgroup reads its solve's (n, kpt) and runs the

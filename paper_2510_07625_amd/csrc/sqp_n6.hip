@@ -12,7 +12,10 @@ hipError_t launch_sqp_n6(int kpt, bool f64, int grid, const KArgs &a, hipStream_
     case 4: hipLaunchKernelGGL((sqp_kernel<6, 2, float>), g, b, 0, s, a); break;
     case 5: hipLaunchKernelGGL((sqp_kernel<6, 2, double>), g, b, 0, s, a); break;
     case 8: hipLaunchKernelGGL((sqp_kernel<6, 4, float>), g, b, 0, s, a); break;
-    case 9: hipLaunchKernelGGL((sqp_kernel<6, 4, double>), g, b, 0, s, a); break;
+    case 9:
+      if (a.mode == kModeKkt) hipLaunchKernelGGL((sqp_kernel<6, 4, double, false, false, true>), g, b, 0, s, a);
+      else hipLaunchKernelGGL((sqp_kernel<6, 4, double>), g, b, 0, s, a);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
