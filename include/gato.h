@@ -157,8 +157,9 @@ typedef struct {
 void gato_default_params(gato_params *p);
 
 /*
- * Device workspace one solve of this shape needs (bytes). Pure host
- * computation; usable for memory-based admission. Returns 0 for invalid input.
+ * Device workspace one solve of this shape needs at most (bytes; the all-FP32
+ * variant's, schur_fp64 = 1 needs less). Pure host computation; usable for
+ * memory-based admission. Returns 0 for invalid input.
  */
 size_t gato_workspace_bytes(int n_dof, int N, const gato_params *p);
 

@@ -62,14 +62,15 @@ struct Layout {
   size_t offA, offB, offD, offT, total;
 };
 
-Layout layout_for(int n, int N) {
+// (FP64: the inverse diagonal blocks and the Schur rows stay in registers.)
+Layout layout_for(int n, int N, bool fp64) {
   const size_t nx = 2 * (size_t)n, nu = (size_t)n;
   Layout l;
   l.offA = 0;
   l.offB = align256(l.offA + (size_t)(N - 1) * nx * nx * sizeof(float));
   l.offD = align256(l.offB + (size_t)(N - 1) * nx * nu * sizeof(float));
-  l.offT = align256(l.offD + (size_t)N * nx * nx * sizeof(float));
-  l.total = align256(l.offT + (size_t)N * nx * nx * sizeof(double));
+  l.offT = fp64 ? l.offD : align256(l.offD + (size_t)N * nx * nx * sizeof(float));
+  l.total = fp64 ? l.offD : align256(l.offT + (size_t)N * nx * nx * sizeof(double));
   return l;
 }
 
@@ -302,7 +303,7 @@ static int check_params(const gato_params *p) {
 size_t gato_workspace_bytes(int n_dof, int N, const gato_params *p) {
   if (!dof_supported(n_dof) || N < 2 || N > GATO_MAX_KNOTS) return 0;
   if (p && p->n_alpha > GATO_MAX_ALPHA) return 0;
-  return layout_for(n_dof, N).total + (size_t)N * 2 * n_dof * sizeof(double) + sizeof(SolveDesc) +
+  return layout_for(n_dof, N, false).total + (size_t)N * 2 * n_dof * sizeof(double) + sizeof(SolveDesc) +
          64 * sizeof(gato_solve_stats);
 }
 
@@ -418,22 +419,23 @@ int gato_batch_create(int M, const gato_robot *robots, const gato_problem *probs
   size_t off = 0;
   int64_t xwords = 0;
   for (int i = 0; i < M; ++i) {
-    const Layout l = layout_for(desc[i].n, desc[i].N);
+    const bool fp64 = prm.schur_fp64 != 0;
+    const Layout l = layout_for(desc[i].n, desc[i].N, fp64);
     desc[i].ws_off = (int64_t)off;
     desc[i].offA = (int64_t)l.offA;
     desc[i].offB = (int64_t)l.offB;
     desc[i].offD = (int64_t)l.offD;
     desc[i].offT = (int64_t)l.offT;
-    // Long solves (four knots per lane group) can split: a workspace per part
-    // and an exchange area.
+    // Long solves (four knots per lane group) can split: an exchange area, and
+    // a workspace per part (FP64 parts keep their blocks in LDS).
     const bool can_split = desc[i].kpt == 4 && (!task || prm.schur_fp64);
-    desc[i].ws_part = can_split ? (int64_t)l.total : 0;
+    desc[i].ws_part = can_split && !fp64 ? (int64_t)l.total : 0;
     desc[i].xch_off = can_split ? xwords : -1;
     if (can_split) {
       xwords += gato::kXWordsPerSolve;
       ++b->n_split;
     }
-    off += l.total * (can_split ? gato::kSplitParts : 1);
+    off += l.total * (desc[i].ws_part ? gato::kSplitParts : 1);
   }
   b->ws_bytes = off;
   b->xwords = (size_t)xwords;

@@ -29,11 +29,11 @@ struct SolveDesc {
   int task;             // the solve has a tip tracking term
   int pad1;
   int64_t ws_off;     // byte offset of this solve's workspace
-  int64_t offA, offB, offD, offT;  // byte offsets inside it: A_k, B_k and the inverse
-                                   // diagonal blocks (float); Schur diagonal rows (double)
-  // Multi-CU split of a long solve (four knots per lane group, FP64 Schur):
-  // bytes of one part's workspace (part j at ws_off + j ws_part) and the word
-  // offset of the solve's exchange area, or -1 when the solve cannot split.
+  int64_t offA, offB, offD, offT;  // byte offsets inside it: A_k, B_k and (all-FP32 variant) the
+                                   // inverse diagonal blocks (float), Schur diagonal rows (double)
+  // Multi-CU split of a long solve (four knots per lane group): bytes of one
+  // part's workspace (part j at ws_off + j ws_part; all-FP32 variant, else 0) and
+  // the word offset of the solve's exchange area, or -1 when the solve cannot split.
   int64_t ws_part;
   int64_t xch_off;
 };
