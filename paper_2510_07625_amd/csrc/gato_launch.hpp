@@ -98,8 +98,10 @@ inline int kpt_for(int n, int N) {
 // Threads of a one-shape launch. Knots that do not exist leave their lane groups
 // idle, so at one knot per lane group the workgroup holds the wavefronts that the
 // batch's longest horizon and its line search (a thread per candidate and knot)
-// need. Up to 256 threads, two workgroups share a CU (256 VGPRs, at most 79 KB of
-// LDS), so that more solves than CUs run together: N = 16 or less in 6-7 DoF.
+// need. Up to 256 threads (N = 16 or less in 6-7 DoF), two workgroups of the FP64
+// joint-space kernels share a CU (256 VGPRs, at most 79 KB of LDS), so that more
+// solves than CUs run together; the 6-7 DoF tip tracking and all-FP32 kernels (85 to
+// 144 KB) gain by their smaller barriers only.
 // One SQP iteration, 6 DoF, N = 8, against 512 threads: 512 solves 92 -> 60 us, one
 // solve 47.5 -> 45.4 (barriers of two wavefronts instead of eight).
 inline int block_threads(int n, int kpt, const KArgs &a) {

@@ -247,7 +247,6 @@ __device__ __forceinline__ double lane_val(double v, int l) {
 // statement that starts with the two wait states a DPP read needs after a VALU
 // write of its source (x is only read inside it).
 #define GATO_NB1(M, C) "v_fmac_f64_dpp %0, %1, %[c" #M "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t"
-#define GATO_NB2(M, A) "v_fmac_f64_dpp %" #A ", %2, %[c" #M "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t"
 #define GATO_C12(c) [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]), [c3] "v"(c[3]), [c4] "v"(c[4]), [c5] "v"(c[5]), \
     [c6] "v"(c[6]), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]), [c11] "v"(c[11])
 #define GATO_C14(c) GATO_C12(c), [c12] "v"(c[12]), [c13] "v"(c[13])
@@ -338,41 +337,26 @@ __device__ __forceinline__ void row_dot1_sub(double &acc, double x, const double
 #undef GATO_DOT8
 #undef GATO_NB8
 
-// acc += sgn * sum_m c[m] x_m with FP32 coefficients converted inside the
-// statement (two temporaries), m = 0..NX-1 in order; the same roundings as
-// the loop acc = fma(sgn c[m], x_m, acc) over the converted c[m].
-#define GATO_NBF(M, T, S) "v_cvt_f64_f32 %[" #T "], %[c" #M "]\n\t"                                \
-  "v_fmac_f64_dpp %0, " S "%[x], %[" #T "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t"
-#define GATO_F14(c) [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]), [c3] "v"(c[3]), [c4] "v"(c[4]),     \
-    [c5] "v"(c[5]), [c6] "v"(c[6]), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]),   \
-    [c11] "v"(c[11]), [c12] "v"(c[12]), [c13] "v"(c[13])
-#define GATO_F12(c) [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]), [c3] "v"(c[3]), [c4] "v"(c[4]),     \
-    [c5] "v"(c[5]), [c6] "v"(c[6]), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]),   \
-    [c11] "v"(c[11])
-#define GATO_DOTF(S)                                                                                      \
-  if constexpr (NX == 14) {                                                                               \
-    asm volatile("s_nop 1\n\t" GATO_NBF(0, ta, S) GATO_NBF(1, tb, S) GATO_NBF(2, ta, S) GATO_NBF(3, tb, S) \
-                 GATO_NBF(4, ta, S) GATO_NBF(5, tb, S) GATO_NBF(6, ta, S) GATO_NBF(7, tb, S)              \
-                 GATO_NBF(8, ta, S) GATO_NBF(9, tb, S) GATO_NBF(10, ta, S) GATO_NBF(11, tb, S)            \
-                 GATO_NBF(12, ta, S) GATO_NBF(13, tb, S)                                                  \
-                 : "+v"(acc), [ta] "=&v"(ta), [tb] "=&v"(tb) : [x] "v"(x), GATO_F14(c));                     \
-  } else {                                                                                                \
-    asm volatile("s_nop 1\n\t" GATO_NBF(0, ta, S) GATO_NBF(1, tb, S) GATO_NBF(2, ta, S) GATO_NBF(3, tb, S) \
-                 GATO_NBF(4, ta, S) GATO_NBF(5, tb, S) GATO_NBF(6, ta, S) GATO_NBF(7, tb, S)              \
-                 GATO_NBF(8, ta, S) GATO_NBF(9, tb, S) GATO_NBF(10, ta, S) GATO_NBF(11, tb, S)            \
-                 : "+v"(acc), [ta] "=&v"(ta), [tb] "=&v"(tb) : [x] "v"(x), GATO_F12(c));                     \
-  }
+// acc += sum_m c[m] x_m with FP32 coefficients converted inside the statement (two
+// temporaries), m = 0..NX-1 in order; the same roundings as the loop
+// acc = fma(c[m], x_m, acc) over the converted c[m].
+#define GATO_NBF(M, T) "v_cvt_f64_f32 %[" #T "], %[c" #M "]\n\t"                                \
+  "v_fmac_f64_dpp %0, %[x], %[" #T "] row_newbcast:" #M " row_mask:0xf bank_mask:0xf\n\t"
 template <int NX>
 __device__ __forceinline__ void row_dot1_f(double &acc, double x, const float *c) {
   static_assert(NX == 12 || NX == 14, "16-lane groups hold 12 or 14 rows");
   double ta, tb;
-  GATO_DOTF("")
-}
-template <int NX>
-__device__ __forceinline__ void row_dot1_sub_f(double &acc, double x, const float *c) {
-  static_assert(NX == 12 || NX == 14, "16-lane groups hold 12 or 14 rows");
-  double ta, tb;
-  GATO_DOTF("-")
+  if constexpr (NX == 14) {
+    asm volatile("s_nop 1\n\t" GATO_NBF(0, ta) GATO_NBF(1, tb) GATO_NBF(2, ta) GATO_NBF(3, tb) GATO_NBF(4, ta)
+                 GATO_NBF(5, tb) GATO_NBF(6, ta) GATO_NBF(7, tb) GATO_NBF(8, ta) GATO_NBF(9, tb) GATO_NBF(10, ta)
+                 GATO_NBF(11, tb) GATO_NBF(12, ta) GATO_NBF(13, tb)
+                 : "+v"(acc), [ta] "=&v"(ta), [tb] "=&v"(tb) : [x] "v"(x), GATO_C14(c));
+  } else {
+    asm volatile("s_nop 1\n\t" GATO_NBF(0, ta) GATO_NBF(1, tb) GATO_NBF(2, ta) GATO_NBF(3, tb) GATO_NBF(4, ta)
+                 GATO_NBF(5, tb) GATO_NBF(6, ta) GATO_NBF(7, tb) GATO_NBF(8, ta) GATO_NBF(9, tb) GATO_NBF(10, ta)
+                 GATO_NBF(11, tb)
+                 : "+v"(acc), [ta] "=&v"(ta), [tb] "=&v"(tb) : [x] "v"(x), GATO_C12(c));
+  }
 }
 // The same over the velocity entries m = NX/2..NX-1 only.
 template <int NX>
@@ -380,42 +364,22 @@ __device__ __forceinline__ void row_dot1_vel_f(double &acc, double x, const floa
   static_assert(NX == 12 || NX == 14, "16-lane groups hold 12 or 14 rows");
   double ta, tb;
   if constexpr (NX == 14) {
-    asm volatile("s_nop 1\n\t" GATO_NBF(7, ta, "") GATO_NBF(8, tb, "") GATO_NBF(9, ta, "") GATO_NBF(10, tb, "")
-                 GATO_NBF(11, ta, "") GATO_NBF(12, tb, "") GATO_NBF(13, ta, "")
+    asm volatile("s_nop 1\n\t" GATO_NBF(7, ta) GATO_NBF(8, tb) GATO_NBF(9, ta) GATO_NBF(10, tb)
+                 GATO_NBF(11, ta) GATO_NBF(12, tb) GATO_NBF(13, ta)
                  : "+v"(acc), [ta] "=&v"(ta), [tb] "=&v"(tb)
                  : [x] "v"(x), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]), [c11] "v"(c[11]),
                    [c12] "v"(c[12]), [c13] "v"(c[13]));
   } else {
-    asm volatile("s_nop 1\n\t" GATO_NBF(6, ta, "") GATO_NBF(7, tb, "") GATO_NBF(8, ta, "") GATO_NBF(9, tb, "")
-                 GATO_NBF(10, ta, "") GATO_NBF(11, tb, "")
+    asm volatile("s_nop 1\n\t" GATO_NBF(6, ta) GATO_NBF(7, tb) GATO_NBF(8, ta) GATO_NBF(9, tb)
+                 GATO_NBF(10, ta) GATO_NBF(11, tb)
                  : "+v"(acc), [ta] "=&v"(ta), [tb] "=&v"(tb)
                  : [x] "v"(x), [c6] "v"(c[6]), [c7] "v"(c[7]), [c8] "v"(c[8]), [c9] "v"(c[9]), [c10] "v"(c[10]),
                    [c11] "v"(c[11]));
   }
 }
-#undef GATO_DOTF
-#undef GATO_F12
-#undef GATO_F14
 #undef GATO_NBF
 
-// d0 += sum over even m of c[m] x_m, d1 += sum over odd m (two independent chains).
-template <int NX>
-__device__ __forceinline__ void row_dot2(double &d0, double &d1, double x, const double *c) {
-  static_assert(NX == 12 || NX == 14, "16-lane groups hold 12 or 14 rows");
-  if constexpr (NX == 14) {
-    asm volatile("s_nop 1\n\t" GATO_NB2(0, 0) GATO_NB2(1, 1) GATO_NB2(2, 0) GATO_NB2(3, 1) GATO_NB2(4, 0)
-                 GATO_NB2(5, 1) GATO_NB2(6, 0) GATO_NB2(7, 1) GATO_NB2(8, 0) GATO_NB2(9, 1) GATO_NB2(10, 0)
-                 GATO_NB2(11, 1) GATO_NB2(12, 0) GATO_NB2(13, 1)
-                 : "+v"(d0), "+v"(d1) : "v"(x), GATO_C14(c));
-  } else {
-    asm volatile("s_nop 1\n\t" GATO_NB2(0, 0) GATO_NB2(1, 1) GATO_NB2(2, 0) GATO_NB2(3, 1) GATO_NB2(4, 0)
-                 GATO_NB2(5, 1) GATO_NB2(6, 0) GATO_NB2(7, 1) GATO_NB2(8, 0) GATO_NB2(9, 1) GATO_NB2(10, 0)
-                 GATO_NB2(11, 1)
-                 : "+v"(d0), "+v"(d1) : "v"(x), GATO_C12(c));
-  }
-}
 #undef GATO_NB1
-#undef GATO_NB2
 #undef GATO_C12
 #undef GATO_C14
 
@@ -484,12 +448,11 @@ __device__ __forceinline__ void gj_dpp(double *row, int lane, std::integer_seque
 }
 #undef GATO_GJ
 
-// The PCG's step-length quotients: a / b through the hardware reciprocal and
-// two Newton steps (about an ulp from the rounded quotient). Every FP64 PCG
-// loop uses it: against the correctly rounded division, whose longer
-// dependent chain sits between the inner products and the vector updates of
-// every iteration, it takes 1.4% off the one-knot-per-group joint-space call,
-// 2.7% off the two-knots-per-group call and 3% off the task-space call.
+// The PCG's reciprocals: the hardware reciprocal and two Newton steps (about an ulp
+// from the rounded one), instead of a correctly rounded division, whose longer
+// dependent chain sits between the inner products and the vector updates of every
+// iteration. The all-FP32 variant with FP64 inner products takes its quotients from
+// it (div_pcg).
 __device__ __forceinline__ double rcp_pcg(double b) {
   double r = __builtin_amdgcn_rcp(b);
   double e = fma(-b, r, 1.0);
@@ -513,35 +476,8 @@ __device__ __forceinline__ R wave_sum(R v) {
   return lane_val(v, 63);
 }
 
-// Two wavefront sums interleaved step by step (each step of one hides the
-// latency of the other's).
-template <class R>
-__device__ __forceinline__ void wave_sum2(R &a, R &b) {
-  a += dpp<0xB1>(a);
-  b += dpp<0xB1>(b);
-  a += dpp<0x4E>(a);
-  b += dpp<0x4E>(b);
-  a += dpp<0x141>(a);
-  b += dpp<0x141>(b);
-  a += dpp<0x140>(a);
-  b += dpp<0x140>(b);
-  a += bcast<0x142, 0xA>(a);
-  b += bcast<0x142, 0xA>(b);
-  a += bcast<0x143, 0xC>(a);
-  b += bcast<0x143, 0xC>(b);
-  a = lane_val(a, 63);
-  b = lane_val(b, 63);
-}
-
 // Sum over the workgroup of NV values: butterfly inside each wavefront, then a
 // fixed-order sum of the per-wavefront partials.
-// Pairwise sum of W values in a fixed order: ((v0 + v1) + (v2 + v3)) + ...
-template <int W>
-__device__ __forceinline__ double pair_tree(const double *v) {
-  if constexpr (W == 1) return v[0];
-  else return pair_tree<W / 2>(v) + pair_tree<W / 2>(v + W / 2);
-}
-
 // The partials travel through LDS as double (exact for float values).
 template <int NV, class V>
 __device__ __forceinline__ void block_sum(double (*red)[3][kBlock / 64], int &buf, V *v) {
@@ -637,9 +573,6 @@ struct OffRows {
   __device__ __forceinline__ void sub(int p, double &y, double xl, double xr, double) const {
     row_dot1_sub<2 * ND>(y, xl, Am[p]);
     row_dot1_sub<2 * ND>(y, xr, Ac[p]);
-  }
-  __device__ __forceinline__ void add_col(int p, double &y, double xr, double) const {
-    row_dot1<2 * ND>(y, xr, Ac[p]);
   }
 };
 // With the joint rows of A_k known to be [I, hI] (the Euler step's), their part
@@ -872,6 +805,9 @@ struct NoExchange {
 // sums. The tip systems are conditioned worse (kappa(P S~) about 2e4): there the
 // pipelined recurrences stop converging near a tolerance of 1e-8 (the cap of
 // 2000 iterations instead of about 300), for 0.96 against 1.00 us per iteration.
+// (The parts of a split tip solve run the pipelined loop all the same, since a barrier
+// more would be a round trip more between workgroups. They reach 1e-9 in the usual
+// count; at 1e-10 some solves of N >= 100 take three to ten times as many.)
 // The loop's time is the latency of its two exchanges through LDS next to the
 // two wavefronts' FMAs, so everything that hangs on the sums (scalars, stopping
 // test) sits where another product is under way; the test is taken after the
@@ -1182,7 +1118,7 @@ __device__ __forceinline__ int pcg_long(PcgBufs<ND, K> &pb, int tid, int lane, i
 // polled with relaxed agent-scope atomics: each access is single-copy atomic
 // and coherent across the XCDs' L2 caches, so a reader that sees the tag sees
 // the half stored with it, and no fence (no whole-L2 write-back or
-// invalidation) is needed. Exchange e uses slot e mod 4 of the writer; a part
+// invalidation) is needed. Exchange e uses slot e mod kXSlots of the writer; a part
 // reuses a slot only after completing later exchanges that every reader of the
 // slot had to take part in. Every wait is bounded.
 constexpr int kXSlot = 104;                   // words: left row [0, 32), right row [32, 64), sums [64, 104)
@@ -3318,8 +3254,8 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
     if (clk) clk[5] = wall_clock64();
 
     // ================= 6. Line search over alpha_i = beta^-i (Eqs. (3), (7)).
-    // (The biases go through the space of the A blocks, read for the last time in
-    // phase 2.)
+    // (The biases go through the space of the A blocks, whose last reads, in phase 5
+    // with tip tracking and caller-given data, the barrier above orders before it.)
     float *kpt_bias = nullptr;
     if constexpr (KPT == 1) {
       static_assert(kBlock / 2 * ND <= BS::LB * NX * NX && BS::kLds, "biases of the trial knots");
@@ -3424,6 +3360,7 @@ __global__ __launch_bounds__(kBlock) void sqp_kernel(KArgs a) {
   constexpr size_t kPart = SPLIT && sizeof(Real) == 8 ? long_part_bytes<ND>() : 0;
   constexpr size_t kBytes = kOne > kPart ? kOne : kPart;
   static_assert(kBytes <= 160 * 1024, "LDS of one workgroup exceeds 160 KB");
+  static_assert(KPT != 1 || TS || sizeof(Real) == 4 || 2 * kBytes <= 160 * 1024, "block_threads: two workgroups to a CU");
   __shared__ __align__(16) char smem[kBytes];
   int sid = a.order ? a.order[blockIdx.x] : a.sid_base + (int)blockIdx.x;
   int part = 0;
@@ -3439,11 +3376,12 @@ __global__ __launch_bounds__(kBlock) void sqp_kernel(KArgs a) {
 
 // Mixed-shape kernel: every workgroup reads its solve's (n, kpt) and runs the
 // matching specialisation, so a batch of uneven DoF and horizon is one launch.
-// The LDS footprint is the largest specialisation's; every specialisation
-// already runs one workgroup per CU, so occupancy is unchanged. (For 3 DoF,
-// two knots per 8-lane group already cover the maximum horizon; the
-// task-space variant is compiled for one and two knots per group, and its
-// long solves (6-7 DoF, N > 64) run only split, in the part-local form.)
+// The LDS footprint is the largest specialisation's, and the workgroup has kBlock
+// threads: one workgroup per CU, where a one-shape launch of short horizons runs two
+// (block_threads). (For 3 DoF, two knots per 8-lane group already cover the maximum
+// horizon; the task-space variant is compiled for one and two knots per group, and
+// its long solves (6-7 DoF, N > 64) run only split, in the part-local form; long
+// solves of caller-given QP data have kernels of their own.)
 template <class Real, bool TS, bool SPLIT>
 constexpr size_t mixed_smem_bytes() {
   size_t m = SPLIT && !TS && sizeof(Real) == 8 ? long_part_bytes<7>() : 0;
