@@ -16,17 +16,20 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgato.so")
 ARCH = os.environ.get("GATO_OFFLOAD_ARCH", "gfx950")
-SOURCES = ["sqp_mixed_f64.hip", "sqp_mixed_f32.hip", "sqp_n7.hip", "sqp_n6.hip", "sqp_n3.hip", "sqp_task.hip", "sqp_mixed_task.hip",
-           "gato_api.hip",
-           "gato_plant.hip", "gato_flops.cpp", "gato_probe.hip"]
+SOURCES = ["sqp_mixed_f64.hip", "sqp_mixed_f32.hip", "sqp_long.hip", "sqp_n7.hip", "sqp_n6.hip", "sqp_n3.hip", "sqp_task.hip",
+           "sqp_mixed_task.hip", "gato_api.hip", "gato_plant.hip", "gato_flops.cpp", "gato_probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-# Loops on a 64-byte line, where it gains: tip tracking's PCG loop (one knot per lane
-# group) is bound by instruction fetch from a start of 4 mod 8 bytes, 1.09 against 1.03
-# us per iteration (N = 32, 7 DoF). The other loops are within 1% either way.
-EXTRA = {"sqp_task.hip": ["-falign-loops=64"], "sqp_mixed_task.hip": ["-falign-loops=64"]}
+# Loops on a 64-byte line, where it gains. The PCG loops are bound by instruction fetch
+# from an unlucky start (8-byte instructions from 4 mod 8 bytes on): us per iteration,
+# aligned against not: tip tracking 7 DoF N = 32 1.03 / 1.09; long solves 7 DoF N = 100
+# on four workgroups 1.95 / 2.00, N = 128 on one 3.70 / 3.81; all-FP32 6 DoF N = 64
+# 1.93 / 2.07. 7 DoF up to N = 64 1% slower and 3 DoF mixed (N = 32 all-FP32 5%
+# slower, N = 128 4% faster): as they are.
+ALIGNED = ("sqp_task.hip", "sqp_mixed_task.hip", "sqp_long.hip", "sqp_n6.hip")
+EXTRA = {src: ["-falign-loops=64"] for src in ALIGNED}
 
 
 def _compile(src: str) -> str:

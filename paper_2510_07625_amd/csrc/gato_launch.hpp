@@ -13,6 +13,9 @@ namespace gato {
 // compiled.
 hipError_t launch_sqp(int nd, int kpt, bool f64, int grid, const KArgs &a, hipStream_t s);
 
+// Its long solves of 6 and 7 DoF (kpt 4).
+hipError_t launch_sqp_n6_long(bool f64, int grid, const KArgs &a, hipStream_t s);
+hipError_t launch_sqp_n7_long(bool f64, int grid, const KArgs &a, hipStream_t s);
 // The same for the task-space variant (tip tracking costs): kpt 1 and 2.
 hipError_t launch_sqp_task(int nd, int kpt, bool f64, int grid, const KArgs &a, hipStream_t s);
 // The mixed-shape kernel of the task-space variant.
