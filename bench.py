@@ -63,6 +63,14 @@ def measured_traffic():
     return float(vals["traffic-bytes-per-launch"])
 
 
+def executed_pcg_flops(n, N):
+    """FLOPs of one PCG iteration as the headline kernel runs it (the algorithmic count takes P and S~ one after
+    the other): two products with D^-1, two with the rows of A, two with its columns, whose joint rows are one entry
+    per lane, and 21 operations per row in the recurrences and inner products."""
+    nx = 2 * n
+    return 2 * nx * nx * (2 * N + 2 * (N - 1)) + 4 * (N - 1) * nx * (n + 1) + 21 * N * nx
+
+
 KERNEL_TRACE_SUMMARY = os.path.join(ROOT, "profiles", "sqp_kernel_7dof_N32_M256_kernel_trace.md")
 
 
@@ -744,13 +752,15 @@ def main():
     flops_launch = sum(g.sqp_iteration_flops(7, 32, params.n_alpha, pcg[i]) for i in range(M))
     achieved = flops_launch / (kern.mean() * 1e-3)
     prof = profiled_kernel(KERNEL_TRACE_SUMMARY)
+    pcg_flops = g.sqp_iteration_flops(7, 32, params.n_alpha, [1]) - g.sqp_iteration_flops(7, 32, params.n_alpha, [0])
+    executed = flops_launch - int(pcg.sum()) * (pcg_flops - executed_pcg_flops(7, 32))
     roof = dict(bound="alu", achieved=achieved / 1e12, peak=PEAK_ALU / 1e12, unit="TFLOP/s",
                 frac=achieved / PEAK_ALU, traffic=measured_traffic(),
                 kernel="gato::sqp_kernel<7, 1, double, false, false>",
                 flops_per_launch=flops_launch, avg_kernel_ms=float(kern.mean()),
+                executed_flops_per_launch=executed, executed_frac=executed / (kern.mean() * 1e-3) / PEAK_ALU,
                 flops_count=dict(per_solve_sqp_iteration=g.sqp_iteration_flops(7, 32, params.n_alpha, [0]),
-                                 per_pcg_iteration=g.sqp_iteration_flops(7, 32, params.n_alpha, [1])
-                                 - g.sqp_iteration_flops(7, 32, params.n_alpha, [0]),
+                                 per_pcg_iteration=pcg_flops, per_pcg_iteration_executed=executed_pcg_flops(7, 32),
                                  pcg_iterations_per_launch=int(pcg.sum())),
                 pcg_iters_per_solve=float(pcg.sum(axis=1).mean()),
                 pcg_iters_slowest_solve=int(pcg.sum(axis=1).max()))
