@@ -3354,7 +3354,7 @@ __device__ __attribute__((always_inline)) inline void sqp_solve(const KArgs &a, 
   }
 }
 
-template <int ND, int KPT, class Real, bool TS = false, bool SPLIT = false, bool KKT = false>
+template <int ND, int KPT, class Real, bool TS = false, bool SPLIT = false>
 __global__ __launch_bounds__(kBlock) void sqp_kernel(KArgs a) {
   constexpr size_t kOne = smem_bytes<ND, KPT, Real, TS>();
   constexpr size_t kPart = SPLIT && sizeof(Real) == 8 ? long_part_bytes<ND>() : 0;
@@ -3371,7 +3371,16 @@ __global__ __launch_bounds__(kBlock) void sqp_kernel(KArgs a) {
     }
   }
   if (sid < 0 || sid >= a.M) return;   // a caller-provided slot out of range: nothing to do
-  sqp_solve<ND, KPT, Real, TS, SPLIT, KKT>(a, sid, part, smem);
+  sqp_solve<ND, KPT, Real, TS, SPLIT>(a, sid, part, smem);
+}
+
+// Long solves of caller-given QP data (FP64).
+template <int ND>
+__global__ __launch_bounds__(kBlock) void kkt_kernel(KArgs a) {
+  __shared__ __align__(16) char smem[smem_bytes<ND, 4, double, false>()];
+  const int sid = a.order ? a.order[blockIdx.x] : a.sid_base + (int)blockIdx.x;
+  if (sid < 0 || sid >= a.M) return;
+  sqp_solve<ND, 4, double, false, false, true>(a, sid, 0, smem);
 }
 
 // Mixed-shape kernel: every workgroup reads its solve's (n, kpt) and runs the

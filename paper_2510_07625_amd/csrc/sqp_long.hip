@@ -12,7 +12,7 @@ template <int ND>
 hipError_t launch(bool f64, int grid, const KArgs &a, hipStream_t s) {
   const dim3 g(grid), b(kBlock);
   if (!f64) hipLaunchKernelGGL((sqp_kernel<ND, 4, float>), g, b, 0, s, a);
-  else if (a.mode == kModeKkt) hipLaunchKernelGGL((sqp_kernel<ND, 4, double, false, false, true>), g, b, 0, s, a);
+  else if (a.mode == kModeKkt) hipLaunchKernelGGL(kkt_kernel<ND>, g, b, 0, s, a);
   else hipLaunchKernelGGL((sqp_kernel<ND, 4, double>), g, b, 0, s, a);
   return hipGetLastError();
 }
